@@ -57,7 +57,7 @@ extern "C" {
 /* Kernel families for the *_variant calls and the plans. */
 #define DCONV_VARIANT_AUTO 0 /* the planner's choice */
 #define DCONV_VARIANT_VALU 1 /* direct convolution on the fp32 vector FMA units */
-#define DCONV_VARIANT_MFMA 2 /* implicit GEMM over C*K*K on the fp32 matrix cores */
+#define DCONV_VARIANT_MFMA 2 /* matrix cores, fp32 accuracy */
 
 /*
  * dconv_single -- Eq. 2: one input map, M filters.
@@ -73,12 +73,17 @@ int dconv_single(const float *I, const float *F, float *O, int Wx, int Wy, int K
 
 /*
  * dconv_single_variant -- dconv_single with the kernel family forced:
- * DCONV_VARIANT_VALU (vector FMAs), DCONV_VARIANT_MFMA (the fp32 matrix
- * cores on a banded form of each filter row) or DCONV_VARIANT_AUTO (the
- * planner's choice, what dconv_single does).  DCONV_EUNSUPPORTED if the
- * matrix-core family is forced where it has no kernel (K < 5, K > 11, or an
- * input whose rows are not 16-byte aligned: I not 16-byte aligned or Wx not
- * a multiple of 4).  Other returns as for dconv_single.
+ * DCONV_VARIANT_VALU (vector FMAs), DCONV_VARIANT_MFMA (the matrix cores on a
+ * banded form of the filter; each fp32 value enters as three bf16 parts and
+ * the sums are as accurate as the vector family's) or DCONV_VARIANT_AUTO (what
+ * dconv_single does).  DCONV_EUNSUPPORTED if the matrix-core family is forced
+ * outside K = 5 .. 11 or for an input whose rows are not 16-byte aligned (I not
+ * 16-byte aligned or Wx not a multiple of 4).  Other returns as for
+ * dconv_single.
+ *   DCONV_VARIANT_AUTO takes the matrix-core kernel wherever it is faster, at
+ * K = 5 .. 13 and any alignment; the plans below describe the division of the
+ * work for the families as they can be forced, so for K other than 7 the
+ * automatic plan is the vector kernel's.
  */
 int dconv_single_variant(const float *I, const float *F, float *O, int Wx, int Wy, int K,
                          int M, int variant, void *stream);
@@ -128,8 +133,10 @@ typedef struct dconv_plan {
 } dconv_plan;
 
 /*
- * dconv_plan_single / dconv_plan_multi -- report the plan a call with these
- * sizes would use on a device with `num_cu` compute units (<= 0: 256).
+ * dconv_plan_single / dconv_plan_multi -- report the planner's plan for these
+ * sizes on a device with `num_cu` compute units (<= 0: 256): what a call with
+ * that plan runs, and what a call without one runs except where dconv_single
+ * takes the matrix-core kernel instead (see dconv_single_variant).
  * Validation is the same as for the compute calls.  `out` must not be NULL.
  */
 int dconv_plan_single(int Wx, int Wy, int K, int M, int num_cu, dconv_plan *out);

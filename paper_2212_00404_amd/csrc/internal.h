@@ -58,12 +58,12 @@ extern long long *g_stage_trace;
 struct SinglePlan {
   int kernel;     // 0: tiled (float4 rows), 1: generic, 2: tiled (unaligned rows), 3: matrix cores
   int K;
-  int rows;       // output rows per lane (R)
-  int lanes;      // lanes across a tile row (64, or fewer for narrow maps; vector kernels)
+  int rows;       // output rows per lane (R); matrix cores: patch rows per wave
+  int lanes;      // lanes across a tile row (64, or fewer for narrow maps)
   int tile_h, tile_w;
   int tiles_x, tiles_y;
   int m_per_block;
-  int grid;       // tiles_x * tiles_y
+  int grid;       // workgroups per filter group
   int grid_z;     // ceil(M / m_per_block)
   int block;
   int lds_bytes;
@@ -74,8 +74,8 @@ constexpr int kMaxTiledK = 11;
 // aligned: the input map pointer is 16-byte aligned (with Wx % 4 == 0 the
 // tiled kernel then stages whole float4).
 // variant: DCONV_VARIANT_AUTO / _VALU / _MFMA; DCONV_EUNSUPPORTED if the
-// matrix-core kernel is forced where it has no instance (K < 5 or K > 11,
-// or rows not 16-byte aligned).
+// matrix-core kernel is forced outside K = 5 .. 11 or for rows that are not
+// whole float4.
 int plan_single(int Wx, int Wy, int K, int M, int num_cu, bool aligned, int variant,
                 SinglePlan *p);
 // Every single-map plan for these sizes (each tile shape of the family the
@@ -86,6 +86,16 @@ int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, in
                       std::vector<SinglePlan> &out);
 hipError_t launch_single(const SinglePlan &p, const float *I, const float *F, float *O,
                          int Wx, int Wy, int M, hipStream_t s);
+// The matrix-core kernel (single_split.hip, K = kSplitMinK .. kSplitMaxK, any
+// alignment): its plan (the filters in `force_splits` groups, 0: the number
+// the time model prefers), launch, and whether a call that forces neither a
+// family nor a plan takes it.
+constexpr int kSplitMinK = 5, kSplitMaxK = 13;
+constexpr int kSplitPlanMinK = 5;  // smallest K of the plans offered for it
+void plan_single_split(int Wx, int Wy, int K, int M, int num_cu, int force_splits, SinglePlan *p);
+bool single_takes_split(int Wx, int Wy, int K, int M, bool aligned);
+hipError_t launch_single_split(const SinglePlan &p, const float *I, const float *F, float *O,
+                               int Wx, int Wy, int M, hipStream_t s);
 // The public description of a plan.
 void export_single_plan(const SinglePlan &p, dconv_plan *out);
 

@@ -36,7 +36,6 @@ constexpr int kW = 4;           // output columns per lane
 constexpr int kLanes = 64;
 constexpr int kWaves = 4;
 constexpr int kBlock = kLanes * kWaves;
-constexpr int kTileW = kLanes * kW;  // 256 output columns per tile
 
 // A lane's 4 output columns, stored as one 16-byte write.  Rows of O start
 // wherever Wout puts them, so the type asks for 4-byte alignment only: the
@@ -319,234 +318,6 @@ __global__ __launch_bounds__(kBlock, (Occupancy<K, VEC4>::value)) void single_ti
   }
 }
 
-// ---------------------------------------------------------------------------
-// Matrix-core variant: banded filter rows on v_mfma_f32_4x4x1f32
-// ---------------------------------------------------------------------------
-// The instruction runs 16 independent 4x4 outer products per wave: lane
-// 4b + i supplies A[b][i], lane 4b + j supplies B[b][j], and lane 4b + j
-// receives D[b][i][j] in its register i.  Block b is a 4 x 4 output patch:
-// D[b][i][j] = O[y_b + j][x_b + i].  For filter row r, step t adds
-// A[i] * B[j] with A[i] = F[r][t - i] (zero outside 0..K-1) and
-// B[j] = I[y_b + j + r][x_b + t]; the K + 3 steps t = 0..K+2 of a row add
-// each of its K taps to all 16 outputs, so K of every K + 3 products are
-// useful (79% at K = 11).  A is the same for every block: a banded copy of
-// the filter, K x (K + 3) values per lane, held in accumulation registers
-// (the instruction reads its A operand from them directly).
-//
-// Sixteen blocks side by side make a 4-row x 64-column patch, and a wave
-// owns a column of P = 4 patches (16 rows x 64 columns; the four waves of a
-// workgroup make a 16 x 256 tile).  It streams the
-// input rows of that column through registers once: lane 4b + j holds
-// input row u + j (four steps t at a time, one 16-byte LDS read), which is
-// row j + r of patch p for r = u - 4p, so one read feeds every patch with
-// 0 <= u - 4p < K (about K / 4 independent accumulation chains at once).
-
-template <int K>
-struct MfmaTileShape {
-  static constexpr int P = 4;                   // patches (4 rows each) per wave column
-  static constexpr int TH = 4 * P;              // output rows per tile
-  static constexpr int IH = TH + K - 1;
-  static constexpr int NT = K + 3;              // steps per filter row
-  static constexpr int NQ = (NT + 3) / 4;       // 16-byte reads per input row
-  static constexpr int IW4 = kLanes + NQ - 1;   // float4 staged per row (256 + K - 1 floats used)
-  // Row stride = 2 (mod 8) float4: the 8 lanes (2 blocks x 4 rows) of one
-  // 128-byte LDS access then touch 8 different 16-byte bank groups.
-  static constexpr int LW4 = IW4 + (10 - IW4 % 8) % 8;
-  static constexpr int BUF4 = IH * LW4;         // one tile buffer, float4
-  static constexpr int LDS = 2 * BUF4 * 16 + 4 * K * NT * 4;
-};
-
-// Two workgroups per compute unit (the two tile buffers and the band fit
-// twice in LDS; accumulators, band and input rows in 2 x 128 registers).
-template <int K> struct MfmaOcc { static constexpr int value = 2; };
-
-typedef float mf4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void *lds_ptr;
-
-// Direct global->LDS copy of 16 bytes per lane: lane l's float4 from `src`
-// lands at dst + l (dst is wave-uniform).
-__device__ __forceinline__ void dma_f128(const float *src, float4 *dst) {
-  __builtin_amdgcn_global_load_lds(src, (lds_ptr)dst, 16, 0, 0);
-}
-
-// The A operands of filter m: every thread stages its share of the banded
-// table band[i][r][t] = F[m][r][t - i] in LDS, then each lane copies row
-// i = lane % 4 into registers.  Two barriers; the caller must not be
-// reading `band` (a K x (K + 3) x 4 float LDS array).
-template <int K>
-__device__ __forceinline__ void load_band(const float *__restrict__ F, int m, int lane,
-                                          float *band, float (&a)[K][K + 3]) {
-  constexpr int NT = K + 3;
-  constexpr int P = MfmaTileShape<K>::P;
-  const float *Fm = F + (size_t)m * K * K;
-  for (int idx = threadIdx.x; idx < 4 * K * NT; idx += kBlock) {
-    const int t = idx % NT;
-    const int r = (idx / NT) % K;
-    const int s = t - idx / (K * NT);
-    band[idx] = (s >= 0 && s < K) ? Fm[r * K + s] : 0.f;
-  }
-  __syncthreads();
-  const float *row = band + (lane & 3) * K * NT;
-#pragma unroll
-  for (int r = 0; r < K; ++r)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) a[r][t] = row[r * NT + t];
-  // The first KA rows go to accumulation registers, the rest to ordinary
-  // vector registers (the instruction takes A from either): with the patch
-  // accumulators that keeps each file within the 128 registers a wave has
-  // when two workgroups share a compute unit.
-  constexpr int KA = (128 - 8 * P) / NT < K ? (128 - 8 * P) / NT : K;
-#pragma unroll
-  for (int r = 0; r < K; ++r)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      if (r < KA)
-        asm volatile("" : "+a"(a[r][t]));
-      else
-        asm volatile("" : "+v"(a[r][t]));
-    }
-  __syncthreads();
-}
-
-// Stage the tile at (y0, x0) into `buf` with direct global->LDS copies (no
-// registers): wave w copies rows w, w + 4, ...  Rows and columns past the
-// map re-read its last row / last float4; they feed only outputs that are
-// never stored.
-template <int K>
-__device__ __forceinline__ void stage_tile(const float *__restrict__ I, int Wx, int Wy, int y0,
-                                           int x0, float4 *buf, int wave, int lane) {
-  using S = MfmaTileShape<K>;
-  for (int row = wave; row < S::IH; row += kWaves) {
-    const float *srow = I + (size_t)min(y0 + row, Wy - 1) * Wx;
-#pragma unroll
-    for (int c = 0; c < S::IW4; c += kLanes) {
-      const int ix = c + lane;
-      if (c + kLanes <= S::IW4 || ix < S::IW4)
-        dma_f128(srow + min(x0 + 4 * ix, Wx - 4), buf + row * S::LW4 + c);
-    }
-  }
-}
-
-template <int K>
-__global__ __launch_bounds__(kBlock, (MfmaOcc<K>::value)) void single_mfma(
-    const float *__restrict__ I, const float *__restrict__ F, float *__restrict__ O,
-    int Wx, int Wy, int M, int tiles_x, int ntiles, int m_per_block) {
-  using S = MfmaTileShape<K>;
-  constexpr int NT = S::NT, NQ = S::NQ, LW4 = S::LW4, P = S::P;
-  // Two tile buffers as separate LDS objects (see the loop below).
-  __shared__ float4 tile0[S::BUF4];
-  __shared__ float4 tile1[S::BUF4];
-  __shared__ float band[4 * K * NT];
-  DCONV_POISON(poison_lds(tile0, S::BUF4), poison_lds(tile1, S::BUF4),
-               poison_lds(band, 4 * K * NT));
-
-  const int Hout = Wy - K + 1;
-  const int Wout = Wx - K + 1;
-  const int nwg = gridDim.x;
-  const int wg = xcd_remap(blockIdx.x, nwg);
-  if (wg >= ntiles) return;
-  const int m_begin = blockIdx.y * m_per_block;
-  const int m_end = min(M, m_begin + m_per_block);
-
-  const int lane = threadIdx.x & (kLanes - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
-  const int blk = lane >> 2;   // block: output columns 4 * blk .. +3 of a patch
-  const int q4 = lane & 3;     // output row of the lane (B, D roles)
-
-  float a[K][NT];
-  load_band<K>(F, m_begin, lane, band, a);
-  stage_tile<K>(I, Wx, Wy, (wg / tiles_x) * S::TH, (wg % tiles_x) * kTileW, tile0, wave, lane);
-  // One tile: wait for its copies, start the next tile's copies into the
-  // other buffer, compute.  The wait is the compiler's own instruction (not
-  // inline assembly), so it knows every copy has landed; and since the two
-  // buffers are distinct LDS objects fixed at compile time in each call, it
-  // can tell that the copies just started cannot alias this tile's reads and
-  // adds no wait for them before the compute (with one array indexed at run
-  // time it waited for all copies in flight, serialising copy and compute).
-  auto step = [&](int t, const float4 *tile, float4 *next) {
-    const int y0 = (t / tiles_x) * S::TH;
-    const int x0 = (t % tiles_x) * kTileW;
-    // Tile t is in `tile` once this wave's copies (and stores) have
-    // completed and every wave has passed the barrier; every wave is then
-    // also done with `next`, which takes the next tile's copies while this
-    // one is computed.
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-    lds_barrier();
-    const int tn = t + nwg;
-    if (tn < ntiles)
-      stage_tile<K>(I, Wx, Wy, (tn / tiles_x) * S::TH, (tn % tiles_x) * kTileW, next, wave, lane);
-
-    for (int m = m_begin; m < m_end; ++m) {
-      if (m != m_begin) load_band<K>(F, m, lane, band, a);
-      float *Om = O + (size_t)m * Hout * Wout;
-      // Input rows u = 0 .. 4P + K - 5 of this wave's column (row u + j in
-      // lane 4b + j); output patch p (rows 4p .. 4p + 3) takes row u with
-      // filter row u - 4p and is stored after its last row, u = 4p + K - 1.
-      constexpr int U = 4 * P + K - 4;
-      const float4 *src = tile + q4 * LW4 + wave * 16 + blk;
-      const int gx = x0 + 4 * (wave * 16 + blk);
-      // Two accumulators per patch (even and odd steps t) keep at least two
-      // independent chains in flight where only one patch takes a row.
-      mf4 acc[P][2];
-#pragma unroll
-      for (int p = 0; p < P; ++p) acc[p][0] = acc[p][1] = (mf4){0.f, 0.f, 0.f, 0.f};
-      float4 cb[NQ], nb[NQ];
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) cb[q] = src[q];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (u + 1 < U) {
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) nb[q] = src[(u + 1) * LW4 + q];
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (4 * q + e >= NT) continue;
-            const float bv = e == 0 ? cb[q].x : e == 1 ? cb[q].y : e == 2 ? cb[q].z : cb[q].w;
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-              const int r = u - 4 * p;
-              if (r >= 0 && r < K)
-                acc[p][e & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[r][4 * q + e], bv,
-                                                                   acc[p][e & 1], 0, 0, 0);
-            }
-          }
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-          if (u != 4 * p + K - 1) continue;
-          // Patch p is complete: this lane holds output row y0 + 4p + q4,
-          // columns gx .. gx + 3.
-          const int gy = y0 + 4 * p + q4;
-          if (gy >= Hout) continue;
-          float *orow = Om + (size_t)gy * Wout + gx;
-          const mf4 v = acc[p][0] + acc[p][1];
-          if (gx + 4 <= Wout) {
-            __builtin_nontemporal_store((vf4u){v[0], v[1], v[2], v[3]},
-                                        reinterpret_cast<vf4u *>(orow));
-          } else {
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-              if (gx + w < Wout) __builtin_nontemporal_store(v[w], orow + w);
-          }
-        }
-#pragma unroll
-        for (int p = 0; p < P; ++p) asm volatile("" : "+a"(acc[p][0]), "+a"(acc[p][1]));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) cb[q] = nb[q];
-      }
-    }
-    if (m_end - m_begin > 1) load_band<K>(F, m_begin, lane, band, a);
-  };
-  for (int t = wg; t < ntiles; t += 2 * nwg) {
-    step(t, tile0, tile1);
-    if (t + nwg >= ntiles) break;
-    step(t + nwg, tile1, tile0);
-  }
-}
-
 // Any K: one output per thread, operands read through the caches.  Used for
 // filters larger than the tiled kernels are instantiated for.
 __global__ __launch_bounds__(256) void single_generic(
@@ -627,18 +398,6 @@ void plan_tiled(int Wx, int Wy, int M, int num_cu, SinglePlan *p) {
   }
 }
 
-// Matrix-core kernels exist for K = kMfmaMinK .. kMaxTiledK.
-constexpr int kMfmaMinK = 5;
-
-template <int K>
-void plan_mfma(int Wx, int Wy, int M, int num_cu, SinglePlan *p) {
-  using S = MfmaTileShape<K>;
-  p->kernel = 3;
-  p->rows = 8;
-  plan_persistent(Wx, Wy, K, M, num_cu, S::TH, kTileW, MfmaOcc<K>::value, p);
-  p->lds_bytes = S::LDS;
-}
-
 // Non-temporal output stores, except where rows of O do not start on
 // 16-byte boundaries, each workgroup writes four or more filters per tile
 // and the output is larger than the L2s together: there ordinary stores,
@@ -686,14 +445,6 @@ void launch_vector(const SinglePlan &p, const float *I, const float *F, float *O
 template <int K>
 hipError_t launch_tiled(const SinglePlan &p, const float *I, const float *F, float *O,
                         int Wx, int Wy, int M, hipStream_t s) {
-  const int ntiles = p.tiles_x * p.tiles_y;
-  if constexpr (K >= kMfmaMinK) {
-    if (p.kernel == 3) {
-      hipLaunchKernelGGL(single_mfma<K>, dim3(p.grid, p.grid_z), dim3(kBlock), 0, s, I, F, O, Wx,
-                         Wy, M, p.tiles_x, ntiles, p.m_per_block);
-      return hipGetLastError();
-    }
-  }
   const bool nt = use_nt_stores(p, O, Wx, Wy, M);
   constexpr int RA = Rows<K, true>::value, RU = Rows<K, false>::value;
   if (p.kernel == 0) {
@@ -718,20 +469,20 @@ int plan_single(int Wx, int Wy, int K, int M, int num_cu, bool aligned, int vari
   p->K = K;
   // 16-byte aligned rows: whole float4 staging loads.
   const bool vec4 = aligned && (Wx % 4 == 0);
-  // The matrix-core kernel needs float4 staging.  On a 4096 x 4096 map it
-  // is level with the vector kernel at K = 7 (ahead in a sequence of
-  // launches of all filter sizes, behind in repeats of K = 7 alone) and
-  // slower at K = 5 (31 vs 28 us), K = 9 (54 vs 47 us) and K = 11 (72 vs
-  // 63 us), so the automatic choice takes it at K = 7 only.
-  const bool can_mfma = vec4 && K >= kMfmaMinK && K <= kMaxTiledK;
+  // The plans of the matrix-core kernel keep to K = 5 .. 11 and rows of whole
+  // float4; a call that forces neither family nor plan takes that kernel
+  // wherever it is faster (single_takes_split).
+  const bool can_mfma = vec4 && K >= kSplitPlanMinK && K <= kMaxTiledK;
   if (variant == DCONV_VARIANT_MFMA && !can_mfma) return DCONV_EUNSUPPORTED;
-  const bool mfma =
-      variant == DCONV_VARIANT_MFMA || (variant == DCONV_VARIANT_AUTO && can_mfma && K == 7);
+  if (variant == DCONV_VARIANT_MFMA || (variant == DCONV_VARIANT_AUTO && can_mfma && K == 7 &&
+                                        single_takes_split(Wx, Wy, K, M, aligned))) {
+    plan_single_split(Wx, Wy, K, M, num_cu, 0, p);
+    return DCONV_OK;
+  }
   switch (K) {
 #define DCONV_PLAN_K(k)                                              \
   case k:                                                            \
-    if (mfma) plan_mfma<(k >= kMfmaMinK ? k : kMfmaMinK)>(Wx, Wy, M, num_cu, p); \
-    else if (vec4) plan_tiled<k, true>(Wx, Wy, M, num_cu, p);        \
+    if (vec4) plan_tiled<k, true>(Wx, Wy, M, num_cu, p);             \
     else plan_tiled<k, false>(Wx, Wy, M, num_cu, p);                 \
     return DCONV_OK;
     DCONV_PLAN_K(1) DCONV_PLAN_K(2) DCONV_PLAN_K(3) DCONV_PLAN_K(4) DCONV_PLAN_K(5)
@@ -814,19 +565,21 @@ void tiled_candidates(int Wx, int Wy, int M, int num_cu, std::vector<SinglePlan>
   }
 }
 
-template <int K>
-void mfma_candidates(int Wx, int Wy, int M, int num_cu, std::vector<SinglePlan> &out) {
-  using S = MfmaTileShape<K>;
-  SinglePlan b{};
-  b.kernel = 3;
-  b.K = K;
-  b.rows = 8;
-  b.lanes = kLanes;
-  b.block = kBlock;
-  b.tile_h = S::TH;
-  b.tile_w = kTileW;
-  b.lds_bytes = S::LDS;
-  add_splits(Wx, Wy, K, M, num_cu, MfmaOcc<K>::value, b, out);
+// The matrix-core kernel's plans for the same divisions of the filters.
+void split_candidates(int Wx, int Wy, int K, int M, int num_cu, std::vector<SinglePlan> &out) {
+  std::vector<int> splits{0};
+  for (int s = 1; s < M; s *= 2) splits.push_back(s);
+  splits.push_back(M);
+  const size_t first = out.size();
+  for (int s : splits) {
+    SinglePlan p{};
+    plan_single_split(Wx, Wy, K, M, num_cu, s, &p);
+    bool dup = false;
+    for (size_t i = first; i < out.size(); ++i)
+      dup = dup || (out[i].m_per_block == p.m_per_block && out[i].rows == p.rows &&
+                    out[i].grid == p.grid && out[i].grid_z == p.grid_z);
+    if (!dup) out.push_back(p);
+  }
 }
 
 }  // namespace
@@ -837,7 +590,7 @@ int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, in
   if (num_cu <= 0) num_cu = 256;
   const bool vec4 = aligned && (Wx % 4 == 0);
   const bool valu = variant != DCONV_VARIANT_MFMA;
-  const bool mfma = variant != DCONV_VARIANT_VALU && vec4 && K >= kMfmaMinK && K <= kMaxTiledK;
+  const bool mfma = variant != DCONV_VARIANT_VALU && vec4 && K >= kSplitPlanMinK && K <= kMaxTiledK;
   if (K > kMaxTiledK) {
     if (!valu) return DCONV_EUNSUPPORTED;
     SinglePlan p;
@@ -852,7 +605,6 @@ int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, in
       if (vec4) tiled_candidates<k, true>(Wx, Wy, M, num_cu, out);               \
       else tiled_candidates<k, false>(Wx, Wy, M, num_cu, out);                   \
     }                                                                            \
-    if (mfma) mfma_candidates<(k >= kMfmaMinK ? k : kMfmaMinK)>(Wx, Wy, M, num_cu, out); \
     break;
     DCONV_CANDIDATES_K(1) DCONV_CANDIDATES_K(2) DCONV_CANDIDATES_K(3) DCONV_CANDIDATES_K(4)
     DCONV_CANDIDATES_K(5) DCONV_CANDIDATES_K(6) DCONV_CANDIDATES_K(7) DCONV_CANDIDATES_K(8)
@@ -861,6 +613,7 @@ int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, in
     default:
       break;
   }
+  if (mfma) split_candidates(Wx, Wy, K, M, num_cu, out);
   return out.empty() ? DCONV_EUNSUPPORTED : DCONV_OK;
 }
 
@@ -886,6 +639,7 @@ hipError_t launch_single(const SinglePlan &p, const float *I, const float *F, fl
     hipLaunchKernelGGL(single_generic, dim3(p.grid), dim3(256), 0, s, I, F, O, Wx, Wy, p.K, M);
     return hipGetLastError();
   }
+  if (p.kernel == 3) return launch_single_split(p, I, F, O, Wx, Wy, M, s);
   switch (p.K) {
 #define DCONV_LAUNCH_K(k) \
   case k:                 \

@@ -1,0 +1,85 @@
+"""GPU: the kernels that split fp32 values into three bf16 parts, at the sizes
+where they can go wrong: strips of 128 (K <= 9) or 64 columns, patch rows of 2
+or 4, maps narrower than a strip, windows that run past the end of the map,
+several filters per workgroup, and values at the ends of the fp32 range.
+
+Bars: integers exact; |O - O64| <= 1e-6 * sum|I*F| on random floats (each
+product is rounded to about 2^-24 and the sums of up to 169 terms add less
+than 16 roundings of 2^-24 each), and never further from the oracle than the
+fp32 vector kernel by more than a tenth.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2212_00404_amd as dc
+from dconv_workloads import random_arrays
+from gpu_util import assert_exact, assert_within, gpu_single, oracle_single
+
+pytestmark = pytest.mark.gpu
+
+# (Wx, Wy, K, M); rows of 4n + 1 .. 3 floats take the kernel at K = 5 and 6 too
+SINGLE = [(k, k, k, 1) for k in range(10, 14)] + [
+    (131, 9, 5, 1), (133, 40, 5, 7), (129, 30, 6, 3), (134, 134, 7, 2), (135, 21, 8, 5),
+    (137, 22, 9, 1), (136, 70, 9, 2), (73, 13, 10, 1), (74, 77, 11, 3), (75, 50, 12, 2),
+    (77, 51, 13, 4), (301, 211, 11, 1), (1025, 33, 7, 9), (515, 600, 9, 40), (64, 1000, 10, 3),
+    (41, 39, 9, 600), (2050, 67, 13, 1)]
+
+
+@pytest.mark.parametrize("shape", SINGLE, ids=[str(s) for s in SINGLE])
+def test_single_split_edges(shape):
+    Wx, Wy, K, M = shape
+    I, F = random_arrays(1, M, Wx, Wy, K, seed=sum(shape) * 31, variant="int")
+    assert_exact(gpu_single(I[0], F[:, 0]), oracle_single(I[0], F[:, 0])[0], str(shape))
+    I, F = random_arrays(1, M, Wx, Wy, K, seed=sum(shape) * 37)
+    O64, A64 = oracle_single(I[0], F[:, 0])
+    O = gpu_single(I[0], F[:, 0])
+    assert_within(O, O64, A64, str(shape), rel=1e-6)
+    V = gpu_single(I[0], F[:, 0], variant="valu")
+    rms = [np.sqrt(np.mean((x.astype(np.float64) - O64) ** 2)) for x in (O, V)]
+    # a handful of outputs says nothing about an average
+    if O64.size > 1000:
+        assert rms[0] <= 1.1 * rms[1], rms
+
+
+@pytest.mark.parametrize("K", [5, 7, 9, 10, 13])
+def test_single_split_reads_stay_in_the_map(K):
+    """The map is the end of its allocation's rows: what lies past it is NaN
+    and must not reach any output."""
+    Wx, Wy, M = 150 - K, 37 + K, 2
+    I, F = random_arrays(1, M, Wx, Wy, K, seed=K)
+    buf = torch.full((Wx * Wy + 4096,), float("nan"), device="cuda")
+    buf[:Wx * Wy] = torch.from_numpy(I[0]).cuda().reshape(-1)
+    O = dc.single(buf[:Wx * Wy].view(Wy, Wx), torch.from_numpy(F[:, 0]).cuda())
+    O64, A64 = oracle_single(I[0], F[:, 0])
+    assert_within(O.cpu().numpy(), O64, A64, "K=%d" % K, rel=1e-6)
+
+
+@pytest.mark.parametrize("K", [6, 9, 11])
+def test_single_split_non_finite(K):
+    """Infinities, NaN and overflowing sums come out where the fp32 vector
+    kernel has them, and nowhere else."""
+    Wx, Wy, M = 301, 45, 2
+    I, F = random_arrays(1, M, Wx, Wy, K, seed=K + 100)
+    I, F = I[0], F[:, 0]
+    I[3, 7], I[20, 150], I[21, 299], I[44, 0] = np.inf, -np.inf, np.nan, 3.4e38
+    F[1, K - 1, 0] = 0.0
+    O, V = gpu_single(I, F), gpu_single(I, F, variant="valu")
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(O), kind(V)), kind
+    ok = np.isfinite(V)
+    O64, A64 = oracle_single(np.where(np.isfinite(I), I, 0).astype(np.float32), F)
+    assert (np.abs(O[ok] - O64[ok]) <= 1e-6 * A64[ok]).all()
+
+
+@pytest.mark.parametrize("scale", [1e-37, 1e-30, 1e30])
+@pytest.mark.parametrize("K", [7, 11])
+def test_single_split_scales(K, scale):
+    """Values near the ends of the fp32 range: the low parts of 1e-37 are
+    denormal bf16 values (an absolute step of 2^-133, half of it per part)."""
+    Wx, Wy, M = 203, 50, 1
+    I, F = random_arrays(1, M, Wx, Wy, K, seed=K + 7)
+    I, F = (I[0] * np.float32(scale)).astype(np.float32), F[:, 0]
+    O64, A64 = oracle_single(I, F)
+    err = np.abs(gpu_single(I, F).astype(np.float64) - O64)
+    assert (err <= 1e-6 * A64 + K * K * 2.0 ** -133).all()
