@@ -4,7 +4,7 @@
 #include <cmath>
 #include <vector>
 
-#include "multi_kernels.h"
+#include "multi_split.h"
 
 namespace dconv {
 #ifdef DCONV_STAGE_TRACE
@@ -205,6 +205,108 @@ double estimate(const Candidate &cd, bool mfma, int C, int M, int Wx, int Wy, in
   return tm;
 }
 
+// ---------------------------------------------------------------------------
+// bf16-triple kernels (multi_split.h)
+// ---------------------------------------------------------------------------
+struct SplitConsts { int cc, lds, pix, ks; };
+
+template <int K, int... S>
+void split_consts_k(int i, SplitConsts &c, std::integer_sequence<int, S...>) {
+  ((i == S ? (c = SplitConsts{SplitShapeCfg<K, S>::CC, SplitShapeCfg<K, S>::LDS_BYTES,
+                              SplitShapeCfg<K, S>::PIX, SplitShapeCfg<K, S>::KS}, 0) : 0), ...);
+}
+
+SplitConsts split_consts(int i, int K) {
+  SplitConsts c{};
+  constexpr auto seq = std::make_integer_sequence<int, kNumSplit>{};
+  switch (K) {
+    case 1: split_consts_k<1>(i, c, seq); break;
+    case 2: split_consts_k<2>(i, c, seq); break;
+    case 3: split_consts_k<3>(i, c, seq); break;
+    case 4: split_consts_k<4>(i, c, seq); break;
+    case 5: split_consts_k<5>(i, c, seq); break;
+    case 6: split_consts_k<6>(i, c, seq); break;
+    case 7: split_consts_k<7>(i, c, seq); break;
+    default: break;
+  }
+  return c;
+}
+
+// The output tile of at most `cap` pixels whose input tile holds at most `pix`:
+// the fewest tiles, the input tile counted a quarter.
+TileChoice choose_split_tile(int Hout, int Wout, int cap, int pix, int K) {
+  TileChoice best{1, 1, Wout, Hout, 0};
+  double best_cost = 0;
+  for (int tpx = 1; tpx <= cap && tpx <= Wout; ++tpx) {
+    int tpy = std::min(cap / tpx, pix / (tpx + K - 1) - (K - 1));
+    tpy = std::min(tpy, Hout);
+    if (tpy < 1) continue;
+    const int tx = (Wout + tpx - 1) / tpx, ty = (Hout + tpy - 1) / tpy;
+    // the least height that gives as many rows of tiles
+    tpy = (Hout + ty - 1) / ty;
+    // rows that break inside the 16 lanes of an LDS access conflict in its banks
+    const double cost = (double)tx * ty * (cap + 0.25 * (tpy + K - 1) * (tpx + K - 1)) *
+                        (tpx % 32 == 0 ? 1.0 : tpx % 16 == 0 ? 1.03 : 1.15);
+    if (best_cost == 0 || cost < best_cost) {
+      best_cost = cost;
+      best = TileChoice{tpy, tpx, tx, ty, (int64_t)tx * ty * cap};
+    }
+  }
+  return best;
+}
+
+void enumerate_split(int C, int M, int Wx, int Wy, int K, int num_cu,
+                     std::vector<std::pair<double, MultiPlan>> &out) {
+  if (K > kSplitMaxFilter) return;
+  if ((int64_t)Wx * Wy >= (int64_t(1) << 29)) return;  // 32-bit byte offsets
+  const int Hout = Wy - K + 1, Wout = Wx - K + 1;
+  for (int i = 0; i < kNumSplit; ++i) {
+    const SplitShape sh = kSplitShapes[i];
+    const SplitConsts sc = split_consts(i, K);
+    if (sc.cc == 0) continue;
+    const int MT = 32 * sh.WM, PT = 32 * sh.NB * sh.WN, NW = sh.WM * sh.WN * sh.WK;
+    if ((int64_t)MT * C * K * K >= (int64_t(1) << 29)) continue;
+    const TileChoice t = choose_split_tile(Hout, Wout, PT, sc.pix, K);
+    const int64_t blocks = (int64_t)t.tiles_x * t.tiles_y * ((M + MT - 1) / MT);
+    const int stages = (C + sc.cc - 1) / sc.cc;
+    // Microseconds: a launch; per round of workgroups (one per compute unit)
+    // its set-up, first stage and stores; per stage the pairs of items of a
+    // SIMD's two waves, the barrier, and the input units and filter bytes to
+    // fetch.  Fitted to every shape's times on 110 layers (19 benchmark
+    // layers, 91 random ones of 32 to 512 channels and filters, maps 7 to 512
+    // wide, K = 1 .. 7): 9% off in the root mean square.
+    const double pair = sh.NB == 2 ? 0.243 : 0.127;
+    const int64_t rounds = (blocks + num_cu - 1) / num_cu;
+    const double share = (double)((sc.ks + sh.WK - 1) / sh.WK);
+    const int units = sc.cc / 8 * (((t.tpy + K - 1) * (t.tpx + K - 1) + 63) / 64);
+    const double kib = sc.cc * K * K * MT / 1024.0;
+    const double us =
+        1.25 + rounds * (5.13 + 0.013 * (sh.WK - 1) +
+                         stages * (0.24 + 2 * share * pair + 0.047 * units + 0.0049 * kib));
+    // On the same layers a clock of estimate() is 0.62 ns (0.32 to 1.3 for nine
+    // in ten), so these kernels are taken where they come out 15% faster:
+    // geometric mean of the times 0.89 of the fp32 kernels' (0.87 for
+    // the faster of the two each time), one layer slower (1.10).
+    const double tm = us * 1900.0;
+    MultiPlan p{};
+    p.variant = DCONV_VARIANT_MFMA;
+    p.kernel = kSplitKernel + i;
+    p.K = K;
+    p.tile_m = MT;
+    p.tpy = t.tpy;
+    p.tpx = t.tpx;
+    p.tiles_x = t.tiles_x;
+    p.tiles_y = t.tiles_y;
+    p.chunk_c = sc.cc;
+    p.waves_c = sh.WK;
+    p.grid_x = (int)blocks;
+    p.grid_y = p.grid_z = 1;
+    p.block = 64 * NW;
+    p.lds_bytes = sc.lds;
+    out.emplace_back(tm, p);
+  }
+}
+
 // Every workgroup shape of one family whose LDS footprint fits, with the
 // time model's estimate, in a fixed order.
 void enumerate_family(int C, int M, int Wx, int Wy, int K, bool mfma, int num_cu,
@@ -295,8 +397,18 @@ int plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_cu, Mul
   }
   if (variant == DCONV_VARIANT_VALU) return plan_family(C, M, Wx, Wy, K, false, num_cu, p);
   // Automatic: the matrix cores deliver twice the fp32 rate of unpacked
-  // vector FMAs, so they are preferred wherever a kernel exists.
-  if (K <= kMfmaMaxK && plan_family(C, M, Wx, Wy, K, true, num_cu, p) == DCONV_OK) return DCONV_OK;
+  // vector FMAs, so they are preferred wherever a kernel exists; the fp32
+  // instructions and the bf16 triples by their estimates.
+  std::vector<std::pair<double, MultiPlan>> all;
+  if (K <= kMfmaMaxK) enumerate_family(C, M, Wx, Wy, K, true, num_cu, all);
+  enumerate_split(C, M, Wx, Wy, K, num_cu, all);
+  if (!all.empty()) {
+    size_t b = 0;
+    for (size_t k = 1; k < all.size(); ++k)
+      if (all[k].first < all[b].first) b = k;
+    *p = all[b].second;
+    return DCONV_OK;
+  }
   return plan_family(C, M, Wx, Wy, K, false, num_cu, p);
 }
 
@@ -322,6 +434,7 @@ int multi_candidates(int C, int M, int Wx, int Wy, int K, int variant, int num_c
   std::vector<std::pair<double, MultiPlan>> all;
   if ((variant == DCONV_VARIANT_AUTO || variant == DCONV_VARIANT_MFMA) && K <= kMfmaMaxK)
     enumerate_family(C, M, Wx, Wy, K, true, num_cu, all);
+  if (variant == DCONV_VARIANT_AUTO) enumerate_split(C, M, Wx, Wy, K, num_cu, all);
   if (variant == DCONV_VARIANT_AUTO || variant == DCONV_VARIANT_VALU)
     enumerate_family(C, M, Wx, Wy, K, false, num_cu, all);
   out.clear();
@@ -350,6 +463,18 @@ hipError_t launch_multi(const MultiPlan &p, const float *I, const float *F, floa
   if (p.kernel == kGenericKernel) {
     hipLaunchKernelGGL(multi_generic, dim3(p.grid_x), dim3(256), 0, st, I, F, O, C, M, Wx, Wy, p.K);
     return hipGetLastError();
+  }
+  if (p.variant == DCONV_VARIANT_MFMA && p.kernel >= kSplitKernel) {
+    switch (p.K) {
+      case 1: return launch_split_k1(p, I, F, O, a, st);
+      case 2: return launch_split_k2(p, I, F, O, a, st);
+      case 3: return launch_split_k3(p, I, F, O, a, st);
+      case 4: return launch_split_k4(p, I, F, O, a, st);
+      case 5: return launch_split_k5(p, I, F, O, a, st);
+      case 6: return launch_split_k6(p, I, F, O, a, st);
+      case 7: return launch_split_k7(p, I, F, O, a, st);
+      default: return hipErrorInvalidValue;
+    }
   }
   if (p.variant == DCONV_VARIANT_MFMA) {
     switch (p.K) {

@@ -68,6 +68,19 @@ DCONV_MFMA_LAUNCHER(8);
 DCONV_MFMA_LAUNCHER(9);
 DCONV_MFMA_LAUNCHER(10);
 DCONV_MFMA_LAUNCHER(11);
+// The bf16-triple kernels (multi_split.h, K <= kSplitMaxFilter): plan kernel ids
+// from kSplitKernel.
+#define DCONV_SPLIT_LAUNCHER(K)                                                              \
+  hipError_t launch_split_k##K(const MultiPlan &p, const float *I, const float *F, float *O, \
+                               const TileArgs &a, hipStream_t st)
+DCONV_SPLIT_LAUNCHER(1);
+DCONV_SPLIT_LAUNCHER(2);
+DCONV_SPLIT_LAUNCHER(3);
+DCONV_SPLIT_LAUNCHER(4);
+DCONV_SPLIT_LAUNCHER(5);
+DCONV_SPLIT_LAUNCHER(6);
+DCONV_SPLIT_LAUNCHER(7);
+constexpr int kSplitKernel = 16, kSplitMaxFilter = 7;
 
 namespace {
 

@@ -14,7 +14,8 @@ import torch
 
 import paper_2212_00404_amd as dc
 from dconv_workloads import random_arrays
-from gpu_util import assert_exact, assert_within, gpu_single, oracle_single
+from gpu_util import (assert_exact, assert_within, gpu_single, oracle_multi,
+                      oracle_single)
 
 pytestmark = pytest.mark.gpu
 
@@ -83,3 +84,72 @@ def test_single_split_scales(K, scale):
     O64, A64 = oracle_single(I, F)
     err = np.abs(gpu_single(I, F).astype(np.float64) - O64)
     assert (err <= 1e-6 * A64 + K * K * 2.0 ** -133).all()
+
+
+# (C, M, Wx, Wy, K): channel counts around the stages of 8 to 128, filters
+# around the tiles of 32 and 64, tiles cut by both edges, more than one round
+# of stages, an odd number of channel-tap items (K = 3, 5, 7 with 8-channel
+# stages)
+MULTI = [(8, 32, 20, 20, 3), (16, 33, 35, 18, 3), (17, 64, 34, 10, 3), (33, 65, 19, 37, 3),
+         (31, 31, 40, 21, 5), (9, 70, 37, 22, 5), (24, 40, 40, 30, 7), (15, 33, 20, 17, 7),
+         (40, 96, 50, 20, 2), (7, 5, 36, 35, 4), (20, 36, 39, 38, 6), (130, 40, 33, 9, 1),
+         (1, 64, 300, 17, 3), (100, 1, 66, 70, 3), (3, 2, 4, 4, 4)]
+
+
+def split_plans(C, M, Wx, Wy, K):
+    return [p for p in dc.plan_multi_candidates(C, M, Wx, Wy, K) if 16 <= p["kernel"] < 99]
+
+
+@pytest.mark.parametrize("layer", MULTI, ids=[str(s) for s in MULTI])
+def test_multi_split_every_plan(layer):
+    """Integers exact in every shape; floats within 3e-6 * sum|I*F| (sums of up
+    to 1000 terms, at most 100 roundings of 2^-24 each) and no further from
+    the oracle than the fp32 kernels by more than a tenth."""
+    C, M, Wx, Wy, K = layer
+    plans = split_plans(*layer)
+    assert plans
+    I, F = random_arrays(C, M, Wx, Wy, K, seed=sum(layer) * 41, variant="int")
+    It, Ft = torch.from_numpy(I).cuda(), torch.from_numpy(F).cuda()
+    O64 = oracle_multi(I, F)[0]
+    for p in plans:
+        assert_exact(dc.multi(It, Ft, plan=p).cpu().numpy(), O64, "%r %r" % (layer, p))
+    I, F = random_arrays(C, M, Wx, Wy, K, seed=sum(layer) * 43)
+    It, Ft = torch.from_numpy(I).cuda(), torch.from_numpy(F).cuda()
+    O64, A64 = oracle_multi(I, F)
+    rms = lambda O: np.sqrt(np.mean((O.astype(np.float64) - O64) ** 2))
+    base = rms(dc.multi(It, Ft, variant="mfma").cpu().numpy())
+    for p in plans:
+        O = dc.multi(It, Ft, plan=p).cpu().numpy()
+        assert_within(O, O64, A64, "%r %r" % (layer, p), rel=3e-6)
+        if O64.size > 1000:
+            assert rms(O) <= 1.1 * base, (p, rms(O), base)
+
+
+@pytest.mark.parametrize("layer", [(17, 33, 21, 19, 3), (9, 34, 23, 20, 5), (70, 5, 33, 9, 1)])
+def test_multi_split_reads_stay_in_the_tensors(layer):
+    """What lies before and after both tensors is NaN and reaches no output."""
+    C, M, Wx, Wy, K = layer
+    I, F = random_arrays(C, M, Wx, Wy, K, seed=sum(layer))
+    def framed(x):
+        buf = torch.full((x.size + 2048,), float("nan"), device="cuda")
+        buf[1024:1024 + x.size] = torch.from_numpy(x).cuda().reshape(-1)
+        return buf[1024:1024 + x.size].view(x.shape)
+    It, Ft = framed(I), framed(F)
+    O64, A64 = oracle_multi(I, F)
+    for p in split_plans(*layer):
+        assert_within(dc.multi(It, Ft, plan=p).cpu().numpy(), O64, A64, str(p), rel=3e-6)
+
+
+def test_multi_split_non_finite():
+    C, M, Wx, Wy, K = 20, 40, 37, 21, 3
+    I, F = random_arrays(C, M, Wx, Wy, K, seed=77)
+    I[3, 5, 9], I[19, 20, 36], I[0, 0, 0] = np.inf, np.nan, 3.4e38
+    F[7, 2, 1, 1], F[39, 19, 2, 2], F[11, 3] = -np.inf, 3e38, 0.0
+    It, Ft = torch.from_numpy(I).cuda(), torch.from_numpy(F).cuda()
+    V = dc.multi(It, Ft, variant="valu").cpu().numpy()
+    for p in split_plans(C, M, Wx, Wy, K):
+        O = dc.multi(It, Ft, plan=p).cpu().numpy()
+        for kind in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(kind(O), kind(V)), (p, kind)
+        ok = np.isfinite(V)
+        assert np.allclose(O[ok], V[ok], rtol=1e-4, atol=1e-3)
