@@ -14,7 +14,7 @@ step or a single workload (one launch per step).
 Prints ONE JSON line: GFLOP/s over the timed steps (2*C*M*K^2*Hout*Wout
 flops per launch; the steps run back to back with HIP events only around the
 whole timed region), the per-launch durations with each launch's roofline
-(attainable = min(157.3 TFLOP/s, flop/byte x 8 TB/s)) from a second pass of
+(attainable = min(P, flop/byte x 8 TB/s), P = 157.3 TFLOP/s (419.4 for kernels on bf16 triples)) from a second pass of
 the same steps with a HIP event pair around every launch on the launch
 stream, the roofline of the dominant launch, and the CPU oracle timed on the
 host cores.
@@ -31,6 +31,7 @@ METRIC = "GFLOP/s and % fp32 roofline for dconv_single/dconv_multi (fp32, 1 MI35
 PEAK_FP32_VECTOR_TFLOPS = 157.3      # 256 CU x 2.4 GHz x 256 flop/clk (packed FMA)
 PEAK_FP32_UNPACKED_TFLOPS = 78.6     # one fp32 FMA per lane per clock
 PEAK_FP32_MFMA_TFLOPS = 157.3
+PEAK_SPLIT_MFMA_TFLOPS = 2516.6 / 6  # six dense bf16 products per fp32 product
 PEAK_HBM_GBS = 8000.0
 SWEEP = "single_4096x4096_m1_k3-11"
 DEFAULT_STEP = "dconv_configs"
@@ -54,9 +55,11 @@ def step_names(workload):
     return steps.get(workload, [workload])
 # Sources each kernel family is built from: recorded HBM traffic stays valid
 # while these are unchanged.
-SINGLE_SOURCES = ("single.hip", "xcd.h")
+SINGLE_SOURCES = ("single.hip", "single_split.hip", "split.h", "xcd.h")
 MULTI_SOURCES = ("multi.hip", "multi_kernels.h", "multi_mfma_k1_3.hip", "multi_mfma_k4_6.hip",
-                 "multi_mfma_k7_9.hip", "multi_mfma_k10_11.hip", "xcd.h")
+                 "multi_mfma_k7_9.hip", "multi_mfma_k10_11.hip", "multi_split.h",
+                 "multi_split_k1_3.hip", "multi_split_k4_5.hip", "multi_split_k6_7.hip",
+                 "split.h", "xcd.h")
 
 
 def parse():
@@ -390,6 +393,8 @@ def trace_report(root, workload=DEFAULT_STEP, out_path=None, command=None):
         if m.group(1) == "multi" and "multi_mfma" in r["Kernel_Name"]:
             mf, mb, wm, wc = int(targs[1]), int(targs[2]), int(targs[4]), int(targs[6])
             extra = (mf * mb * wm, wc)
+        elif m.group(1) == "multi" and "multi_split" in r["Kernel_Name"]:
+            extra = (32 * int(targs[2]), int(targs[4]))
         n = key.get((m.group(1), int(targs[0]), grid, int(r["Workgroup_Size_X"])) + extra)
         if n is None:
             continue
@@ -400,7 +405,7 @@ def trace_report(root, workload=DEFAULT_STEP, out_path=None, command=None):
         lines += ["Command:", "", "```", command, "```", ""]
     lines += ["Per launch: rocprofv3 kernel-trace durations of the libdconv kernel (all dispatches "
               "of the run: warm-up, the timed steps, the event-timed pass and the back-to-back "
-              "repeats).  Roofline: attainable = min(157.3 TFLOP/s, flop/byte x 8 TB/s); `frac` = "
+              "repeats).  Roofline: attainable = min(P, flop/byte x 8 TB/s), P = 157.3 TFLOP/s (419.4 for kernels on bf16 triples); `frac` = "
               "achieved / attainable at the average.", "",
               "| workload | kernel | dispatches | avg us | median us | TFLOP/s | bound | frac |",
               "|---|---|---|---|---|---|---|---|"]
@@ -410,7 +415,7 @@ def trace_report(root, workload=DEFAULT_STEP, out_path=None, command=None):
         w = WORKLOADS[n]
         d = sorted(durs[n])
         avg = sum(d) / len(d)
-        rf = kernel_roofline(w, avg, "multi_mfma" in kname[n])
+        rf = kernel_roofline(w, avg, launch_plan(dc, w, "auto", "auto"))
         lines.append("| %s | `%s` | %d | %.2f | %.2f | %.2f | %s | %.3f |" % (
             n, _short(kname[n]), len(d), avg * 1e6, d[len(d) // 2] * 1e6, rf["tflops"],
             rf["bound"], rf["frac"]))
@@ -556,31 +561,47 @@ def launch_plan(dc, w, variant, single_variant):
     """The plan the library uses for workload w (host logic)."""
     if w.kind == "multi":
         return dc.plan_multi(w.C, w.M, w.Wx, w.Wy, w.K, variant)
+    # An automatic call takes the matrix-core kernel from K = 9 on, with the plan
+    # that forcing it gives; the planner's automatic plan names the vector one.
+    if single_variant == "auto" and 9 <= w.K <= 11 and w.Wx % 4 == 0:
+        single_variant = "mfma"
     return dc.plan_single(w.Wx, w.Wy, w.K, w.M, variant=single_variant)
 
 
-def kernel_roofline(w, avg_s, uses_mfma, measured=None):
+def peak_tflops(w, plan):
+    """The fp32 peak of the units that a plan's kernel runs on: the matrix cores
+    on bf16 triples (the matrix-core kernel of the single map, plans from 16 on
+    of multi-channel layers), the fp32 matrix instructions, or the vector units."""
+    if plan["variant"] != 2:
+        return PEAK_FP32_VECTOR_TFLOPS
+    split = w.kind == "single" or plan["kernel"] >= 16
+    return PEAK_SPLIT_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
+
+
+def kernel_roofline(w, avg_s, plan, measured=None):
     """Roofline of one launch of workload w taking avg_s seconds.
 
     Attainable = min(P, AI x 8 TB/s) with AI = flops / compulsory bytes and
-    P = 157.3 TFLOP/s (the fp32 matrix peak for the matrix-core kernels, the
-    packed fp32 vector peak for the vector kernels); the bound is HBM where
+    P = 157.3 TFLOP/s (the fp32 matrix peak, and the packed fp32 vector peak of
+    the vector kernels) or, for the kernels on bf16 triples, a sixth of the bf16
+    matrix peak (419.4); the bound is HBM where
     AI x 8 TB/s is the smaller.  `frac` = achieved / attainable in the bound's
     unit.  With measured peaks (bench.py --peaks, recorded in
     profiles/peaks.json) the same launch is also given against them."""
     tf = w.flops / avg_s / 1e12
     gbs = w.compulsory_bytes / avg_s / 1e9
     ai = w.flops / w.compulsory_bytes
-    peak = PEAK_FP32_MFMA_TFLOPS if uses_mfma else PEAK_FP32_VECTOR_TFLOPS
+    uses_mfma = plan["variant"] == 2
+    peak = peak_tflops(w, plan)
     hbm_roof = ai * PEAK_HBM_GBS / 1e3
     attainable = min(peak, hbm_roof)
     out = {"tflops": round(tf, 2), "gbs": round(gbs, 1), "flop_per_byte": round(ai, 2),
            "bound": "hbm" if hbm_roof < peak else ("mfma" if uses_mfma else "alu"),
            "attainable_tflops": round(attainable, 2), "frac": round(tf / attainable, 4),
-           "frac_fp32_peak": round(tf / peak, 4), "frac_hbm": round(gbs / PEAK_HBM_GBS, 4)}
+           "frac_fp32_peak": round(tf / PEAK_FP32_MFMA_TFLOPS, 4), "frac_hbm": round(gbs / PEAK_HBM_GBS, 4)}
     if not uses_mfma:
         out["frac_unpacked_fp32"] = round(tf / PEAK_FP32_UNPACKED_TFLOPS, 4)
-    if measured:
+    if measured and peak != PEAK_SPLIT_MFMA_TFLOPS:
         mp = measured.get("mfma_f32_32x32_tflops" if uses_mfma else "fma_fp32_tflops")
         bw = measured.get("hbm_copy_gbs")
         if mp and bw:
@@ -906,7 +927,7 @@ def main():
         ent = {"workload": w.name, "kernel_family": "mfma" if plan["variant"] == 2 else "valu",
                "avg_us": round(avg_s * 1e6, 2),
                "median_us": round(float(np.median(d)) * 1e3, 2)}
-        ent.update(kernel_roofline(w, avg_s, plan["variant"] == 2, measured_peaks))
+        ent.update(kernel_roofline(w, avg_s, plan, measured_peaks))
         per_kernel.append(ent)
 
     # Warm figures: each launch repeated back to back on the same buffers
@@ -945,7 +966,7 @@ def main():
                 "bytes_per_launch": w.compulsory_bytes}
     else:
         achieved = w.flops / (pk["avg_us"] * 1e-6) / 1e12
-        peak = PEAK_FP32_MFMA_TFLOPS if uses_mfma else PEAK_FP32_VECTOR_TFLOPS
+        peak = round(peak_tflops(w, launch_plan(dc, w, args.variant, single_variant(w))), 1)
         roof = {"bound": pk["bound"], "achieved": round(achieved, 2),
                 "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "traffic": traffic, "kernel": w.name,
@@ -1113,7 +1134,7 @@ def write_step_report(out, path):
              "Step: %.2f GFLOP/s (%.4f ms per step over %d steps; `value` of the bench line).  "
              "Per launch: HIP events around every launch of a second pass of the same steps "
              "(avg), and the same launch repeated on its own buffers (back to back).  Roofline: "
-             "attainable = min(157.3 TFLOP/s, flop/byte x 8 TB/s), `frac` = achieved / attainable."
+             "attainable = min(P, flop/byte x 8 TB/s), P = 157.3 TFLOP/s (419.4 for kernels on bf16 triples), `frac` = achieved / attainable."
              % (out["value"], out["ms_per_step"], out["steps"]), ""]
     head = "| workload | family | avg us | back to back us | TFLOP/s | bound | frac |"
     sep = "|---|---|---|---|---|---|---|"

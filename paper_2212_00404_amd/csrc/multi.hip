@@ -2,6 +2,7 @@
 // tile, channels per stage, time model) and launch_multi (paper, Section 3.2).
 #include <algorithm>
 #include <cmath>
+#include <limits>
 #include <vector>
 
 #include "multi_split.h"
@@ -255,7 +256,10 @@ TileChoice choose_split_tile(int Hout, int Wout, int cap, int pix, int K) {
   return best;
 }
 
-void enumerate_split(int C, int M, int Wx, int Wy, int K, int num_cu,
+// Shapes that cannot come out below `bound` whatever their tile are left out
+// (a planner's best so far; a list of every plan passes infinity).  Planning is
+// part of every call: without the bound it took 2.6 us on a 9 x 9 layer.
+void enumerate_split(int C, int M, int Wx, int Wy, int K, int num_cu, double bound,
                      std::vector<std::pair<double, MultiPlan>> &out) {
   if (K > kSplitMaxFilter) return;
   if ((int64_t)Wx * Wy >= (int64_t(1) << 29)) return;  // 32-bit byte offsets
@@ -266,8 +270,7 @@ void enumerate_split(int C, int M, int Wx, int Wy, int K, int num_cu,
     if (sc.cc == 0) continue;
     const int MT = 32 * sh.WM, PT = 32 * sh.NB * sh.WN, NW = sh.WM * sh.WN * sh.WK;
     if ((int64_t)MT * C * K * K >= (int64_t(1) << 29)) continue;
-    const TileChoice t = choose_split_tile(Hout, Wout, PT, sc.pix, K);
-    const int64_t blocks = (int64_t)t.tiles_x * t.tiles_y * ((M + MT - 1) / MT);
+    const int64_t mtiles = (M + MT - 1) / MT;
     const int stages = (C + sc.cc - 1) / sc.cc;
     // Microseconds: a launch; per round of workgroups (one per compute unit)
     // its set-up, first stage and stores; per stage the pairs of items of a
@@ -276,18 +279,26 @@ void enumerate_split(int C, int M, int Wx, int Wy, int K, int num_cu,
     // layers, 91 random ones of 32 to 512 channels and filters, maps 7 to 512
     // wide, K = 1 .. 7): 9% off in the root mean square.
     const double pair = sh.NB == 2 ? 0.243 : 0.127;
-    const int64_t rounds = (blocks + num_cu - 1) / num_cu;
     const double share = (double)((sc.ks + sh.WK - 1) / sh.WK);
-    const int units = sc.cc / 8 * (((t.tpy + K - 1) * (t.tpx + K - 1) + 63) / 64);
     const double kib = sc.cc * K * K * MT / 1024.0;
-    const double us =
-        1.25 + rounds * (5.13 + 0.013 * (sh.WK - 1) +
-                         stages * (0.24 + 2 * share * pair + 0.047 * units + 0.0049 * kib));
+    auto micros = [&](int64_t blocks, int chunks) {  // chunks: 64 input pixels each
+      const int64_t rounds = (blocks + num_cu - 1) / num_cu;
+      const int units = sc.cc / 8 * chunks;
+      return 1.25 + rounds * (5.13 + 0.013 * (sh.WK - 1) +
+                              stages * (0.24 + 2 * share * pair + 0.047 * units + 0.0049 * kib));
+    };
     // On the same layers a clock of estimate() is 0.62 ns (0.32 to 1.3 for nine
     // in ten), so these kernels are taken where they come out 15% faster:
     // geometric mean of the times 0.89 of the fp32 kernels' (0.87 for
     // the faster of the two each time), one layer slower (1.10).
-    const double tm = us * 1900.0;
+    constexpr double kClocks = 1900.0;
+    // at least the tiles that hold all outputs with none to spare
+    if (kClocks * micros(((int64_t)Hout * Wout + PT - 1) / PT * mtiles, 1) >= bound) continue;
+    const TileChoice t = choose_split_tile(Hout, Wout, PT, sc.pix, K);
+    const int64_t blocks = (int64_t)t.tiles_x * t.tiles_y * mtiles;
+    const double tm =
+        kClocks * micros(blocks, ((t.tpy + K - 1) * (t.tpx + K - 1) + 63) / 64);
+    if (tm >= bound) continue;
     MultiPlan p{};
     p.variant = DCONV_VARIANT_MFMA;
     p.kernel = kSplitKernel + i;
@@ -317,6 +328,10 @@ void enumerate_family(int C, int M, int Wx, int Wy, int K, bool mfma, int num_cu
   if (mfma && ((int64_t)C * K * K >= (int64_t(1) << 29) || (int64_t)Wx * Wy >= (int64_t(1) << 29)))
     return;
   const int n = mfma ? kNumMfma : kNumValu;
+  // Several shapes share a tile's number of pixels, and with it the tile: each
+  // is searched once (planning a 512 x 512 layer 7.2 us with a search per shape).
+  struct { int cap; TileChoice tile; } found[std::max(kNumMfma, kNumValu)];
+  int nfound = 0;
   for (int i = 0; i < n; ++i) {
     const Candidate cd = mfma ? mfma_candidate(i, K) : valu_candidate(i);
     // per-wave copies: filter offsets span MT filter rows, input offsets a
@@ -327,7 +342,10 @@ void enumerate_family(int C, int M, int Wx, int Wy, int K, bool mfma, int num_cu
          (int64_t)cd.MT * C * K * K >= (int64_t(1) << 30) ||
          (int64_t)(cd.CC / cd.WC) * Wx * Wy >= (int64_t(1) << 30)))
       continue;
-    const TileChoice t = choose_tile(Hout, Wout, cd.PT, K);
+    int at = 0;
+    while (at < nfound && found[at].cap != cd.PT) ++at;
+    if (at == nfound) found[nfound++] = {cd.PT, choose_tile(Hout, Wout, cd.PT, K)};
+    const TileChoice t = found[at].tile;
     const int IH = t.tpy + K - 1, IW = t.tpx + K - 1;
     int64_t lds_bytes = cd.lds_fixed;
     if (!mfma) {
@@ -400,8 +418,11 @@ int plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_cu, Mul
   // vector FMAs, so they are preferred wherever a kernel exists; the fp32
   // instructions and the bf16 triples by their estimates.
   std::vector<std::pair<double, MultiPlan>> all;
+  all.reserve(kNumMfma + kNumSplit);
   if (K <= kMfmaMaxK) enumerate_family(C, M, Wx, Wy, K, true, num_cu, all);
-  enumerate_split(C, M, Wx, Wy, K, num_cu, all);
+  double bound = std::numeric_limits<double>::infinity();
+  for (const auto &c : all) bound = std::min(bound, c.first);
+  enumerate_split(C, M, Wx, Wy, K, num_cu, bound, all);
   if (!all.empty()) {
     size_t b = 0;
     for (size_t k = 1; k < all.size(); ++k)
@@ -434,7 +455,8 @@ int multi_candidates(int C, int M, int Wx, int Wy, int K, int variant, int num_c
   std::vector<std::pair<double, MultiPlan>> all;
   if ((variant == DCONV_VARIANT_AUTO || variant == DCONV_VARIANT_MFMA) && K <= kMfmaMaxK)
     enumerate_family(C, M, Wx, Wy, K, true, num_cu, all);
-  if (variant == DCONV_VARIANT_AUTO) enumerate_split(C, M, Wx, Wy, K, num_cu, all);
+  if (variant == DCONV_VARIANT_AUTO)
+    enumerate_split(C, M, Wx, Wy, K, num_cu, std::numeric_limits<double>::infinity(), all);
   if (variant == DCONV_VARIANT_AUTO || variant == DCONV_VARIANT_VALU)
     enumerate_family(C, M, Wx, Wy, K, false, num_cu, all);
   out.clear();

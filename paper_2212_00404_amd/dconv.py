@@ -176,6 +176,9 @@ def _check(rc: int):
 
 
 def _require(t: torch.Tensor, name: str, ndim: int):
+    if (isinstance(t, torch.Tensor) and t.dtype is torch.float32 and t.is_cuda
+            and t.dim() == ndim and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor):
         raise ValueError("%s must be a torch.Tensor" % name)
     if t.dtype != torch.float32:
@@ -188,8 +191,10 @@ def _require(t: torch.Tensor, name: str, ndim: int):
         raise ValueError("%s must be contiguous" % name)
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+# What torch.cuda.current_stream(device).cuda_stream and torch.cuda.current_device()
+# give, without the objects they build: a small call is bound by the host.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
 
 
 class _OnDevice:
@@ -211,6 +216,15 @@ class _OnDevice:
             torch.cuda.set_device(self.prev)
 
 
+def _call(fn, t: torch.Tensor, *args) -> int:
+    """``fn(*args, stream)`` on the device and current stream of ``t``."""
+    index = t.get_device()
+    if _current_device() == index:
+        return fn(*args, _raw_stream(index))
+    with _OnDevice(t.device):
+        return fn(*args, _raw_stream(index))
+
+
 def single(I: torch.Tensor, F: torch.Tensor, out: torch.Tensor | None = None,
            variant: str = "auto", plan: dict | None = None) -> torch.Tensor:
     """Eq. 2: ``I[Wy, Wx]``, ``F[M, K, K]`` -> ``O[M, Wy-K+1, Wx-K+1]`` (fp32).
@@ -225,7 +239,7 @@ def single(I: torch.Tensor, F: torch.Tensor, out: torch.Tensor | None = None,
     M, K, K2 = F.shape
     if K != K2:
         raise ValueError("filters must be square, got %r" % (tuple(F.shape),))
-    if F.device != I.device:
+    if F.get_device() != I.get_device():
         raise ValueError("I and F must be on the same device")
     if not (1 <= K <= min(Wx, Wy)):
         raise ValueError("need 1 <= K <= min(Wx, Wy)")
@@ -238,13 +252,12 @@ def single(I: torch.Tensor, F: torch.Tensor, out: torch.Tensor | None = None,
         _require(out, "out", 3)
         if tuple(out.shape) != shape or out.device != I.device:
             raise ValueError("out must be %r on %s" % (shape, I.device))
-    with _OnDevice(I.device):
-        if plan is not None:
-            rc = load().dconv_single_with_plan(I.data_ptr(), F.data_ptr(), out.data_ptr(), Wx, Wy,
-                                               K, M, ctypes.byref(Plan(**plan)), _stream(I.device))
-        else:
-            rc = load().dconv_single_variant(I.data_ptr(), F.data_ptr(), out.data_ptr(), Wx, Wy,
-                                             K, M, _VARIANTS[variant], _stream(I.device))
+    if plan is not None:
+        rc = _call(load().dconv_single_with_plan, I, I.data_ptr(), F.data_ptr(), out.data_ptr(),
+                   Wx, Wy, K, M, ctypes.byref(Plan(**plan)))
+    else:
+        rc = _call(load().dconv_single_variant, I, I.data_ptr(), F.data_ptr(), out.data_ptr(),
+                   Wx, Wy, K, M, _VARIANTS[variant])
     _check(rc)
     return out
 
@@ -263,7 +276,7 @@ def multi(I: torch.Tensor, F: torch.Tensor, out: torch.Tensor | None = None,
     M, C2, K, K2 = F.shape
     if C2 != C or K != K2:
         raise ValueError("filter shape %r does not match input %r" % (tuple(F.shape), tuple(I.shape)))
-    if F.device != I.device:
+    if F.get_device() != I.get_device():
         raise ValueError("I and F must be on the same device")
     if not (1 <= K <= min(Wx, Wy)):
         raise ValueError("need 1 <= K <= min(Wx, Wy)")
@@ -276,14 +289,12 @@ def multi(I: torch.Tensor, F: torch.Tensor, out: torch.Tensor | None = None,
         _require(out, "out", 3)
         if tuple(out.shape) != shape or out.device != I.device:
             raise ValueError("out must be %r on %s" % (shape, I.device))
-    with _OnDevice(I.device):
-        if plan is not None:
-            rc = load().dconv_multi_with_plan(I.data_ptr(), F.data_ptr(), out.data_ptr(), C, M,
-                                              Wx, Wy, K, ctypes.byref(Plan(**plan)),
-                                              _stream(I.device))
-        else:
-            rc = load().dconv_multi_variant(I.data_ptr(), F.data_ptr(), out.data_ptr(), C, M, Wx,
-                                            Wy, K, _VARIANTS[variant], _stream(I.device))
+    if plan is not None:
+        rc = _call(load().dconv_multi_with_plan, I, I.data_ptr(), F.data_ptr(), out.data_ptr(),
+                   C, M, Wx, Wy, K, ctypes.byref(Plan(**plan)))
+    else:
+        rc = _call(load().dconv_multi_variant, I, I.data_ptr(), F.data_ptr(), out.data_ptr(),
+                   C, M, Wx, Wy, K, _VARIANTS[variant])
     _check(rc)
     return out
 
@@ -395,7 +406,7 @@ def probe_latency(footprint_bytes: int, steps: int = 20000, stride_bytes: int = 
     out = torch.zeros(3, dtype=torch.int64, device=dev)
     with _OnDevice(dev):
         _check(load().dconv_probe_latency(chain_d.data_ptr(), steps, out.data_ptr(),
-                                          _stream(dev)))
+                                          torch.cuda.current_stream(dev).cuda_stream))
     torch.cuda.synchronize(dev)
     cyc, ticks, _ = out.tolist()
     return {"footprint_bytes": footprint_bytes, "steps": steps, "stride_bytes": stride_bytes,

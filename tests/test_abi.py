@@ -302,3 +302,15 @@ def test_debug_builds_export_the_api():
                              capture_output=True, text=True, check=True).stdout
         syms = {l.split()[-1] for l in out.splitlines() if " T " in l}
         assert syms == set(dc.EXPORTED) | extra, (lib, syms ^ (set(dc.EXPORTED) | extra))
+
+
+@pytest.mark.parametrize("layer, split", [((64, 64, 512, 512, 3), True), ((93, 131, 61, 45, 5), True),
+                                          ((64, 128, 114, 114, 3), True), ((512, 512, 9, 9, 3), False),
+                                          ((512, 512, 14, 14, 1), False), ((40, 64, 128, 128, 8), False)])
+def test_automatic_multi_plan_is_a_listed_one(layer, split):
+    """The planner leaves out shapes that its bound excludes; the list holds
+    every shape.  Large layers take the kernels on bf16 triples (16 on)."""
+    for num_cu in (32, 256):
+        plan = dc.plan_multi(*layer, num_cu=num_cu)
+        assert plan in dc.plan_multi_candidates(*layer, num_cu=num_cu)
+    assert (plan["variant"] == 2 and plan["kernel"] >= 16) == split
