@@ -420,14 +420,28 @@ int plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_cu, Mul
   std::vector<std::pair<double, MultiPlan>> all;
   all.reserve(kNumMfma + kNumSplit);
   if (K <= kMfmaMaxK) enumerate_family(C, M, Wx, Wy, K, true, num_cu, all);
+  size_t best = 0;
+  for (size_t k = 1; k < all.size(); ++k)
+    if (all[k].first < all[best].first) best = k;
   double bound = std::numeric_limits<double>::infinity();
-  for (const auto &c : all) bound = std::min(bound, c.first);
-  enumerate_split(C, M, Wx, Wy, K, num_cu, bound, all);
   if (!all.empty()) {
-    size_t b = 0;
-    for (size_t k = 1; k < all.size(); ++k)
-      if (all[k].first < all[b].first) b = k;
-    *p = all[b].second;
+    // estimate() is too high for some private-stage plans of eight and sixteen
+    // waves: the two of 26 random layers with such a plan had bf16 triples at
+    // 0.88 and 0.89 of it and ran 1.2 and 1.5 times slower on them (80 x 45, C =
+    // 390, M = 40, K = 3: 21.9 against 26.3 us).  The other 24, at 0.56 to 0.93 of
+    // their fp32 plan, ran 1.0 to 1.7 times faster.
+    const MultiPlan &q = all[best].second;
+    bound = all[best].first * (q.waves_c >= 8 && q.block == 64 * q.waves_c ? 0.85 : 1.0);
+  }
+  const size_t nfp32 = all.size();
+  enumerate_split(C, M, Wx, Wy, K, num_cu, bound, all);
+  for (size_t k = nfp32; k < all.size(); ++k)
+    if (all[k].first < bound) {
+      bound = all[k].first;
+      best = k;
+    }
+  if (!all.empty()) {
+    *p = all[best].second;
     return DCONV_OK;
   }
   return plan_family(C, M, Wx, Wy, K, false, num_cu, p);
