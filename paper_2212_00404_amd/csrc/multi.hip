@@ -425,13 +425,14 @@ int plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_cu, Mul
     if (all[k].first < all[best].first) best = k;
   double bound = std::numeric_limits<double>::infinity();
   if (!all.empty()) {
-    // estimate() is too high for some private-stage plans of eight and sixteen
-    // waves: the two of 26 random layers with such a plan had bf16 triples at
-    // 0.88 and 0.89 of it and ran 1.2 and 1.5 times slower on them (80 x 45, C =
-    // 390, M = 40, K = 3: 21.9 against 26.3 us).  The other 24, at 0.56 to 0.93 of
-    // their fp32 plan, ran 1.0 to 1.7 times faster.
+    // estimate() is too high for some private-stage plans.  Of 71 random layers
+    // the three over such a plan of eight or more waves had bf16 triples at 0.79
+    // to 0.89 of it and ran 1.2 to 1.5 times slower on them (45 x 80, C = 390,
+    // M = 40, K = 3: 21.9 against 26.3 us); of those with four waves one at 0.99
+    // ran 1.04 times slower.  All others ran 1.0 to 2.2 times faster.
     const MultiPlan &q = all[best].second;
-    bound = all[best].first * (q.waves_c >= 8 && q.block == 64 * q.waves_c ? 0.85 : 1.0);
+    const bool priv = q.block == 64 * q.waves_c;
+    bound = all[best].first * (!priv ? 1.0 : q.waves_c >= 8 ? 0.75 : 0.97);
   }
   const size_t nfp32 = all.size();
   enumerate_split(C, M, Wx, Wy, K, num_cu, bound, all);
