@@ -409,6 +409,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void m
     const int ty = fdiv(p, a.tpx, inv_tpx);
     const int gy = py0 + ty, gx = px0 + p - mul24(ty, a.tpx);
     const bool ok = p < npix && gy < Hout && gx < Wout;
+    acc[nb] *= kSplitUnscale;
     float z = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) z = fmaf(0.f, acc[nb][v], z);

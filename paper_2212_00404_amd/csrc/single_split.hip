@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kBlock, 2) void single_split(const float *__restric
             constexpr int QL = NQ - 1;
             if ((jj - QL % ADV + ADV) % ADV == 0 && !(first && jj < QL)) {
               const int s = ((jj - QL) / ADV + NS * ((jj < QL) ? 1 : 0)) % NS;
-              const floatx4 sum = acc[s] + cor[s];
+              const floatx4 sum = (acc[s] + cor[s]) * kSplitUnscale;
               floatx4u r = {sum[0], sum[1], sum[2], sum[3]};
               const int y = y0 + PH * ((w - QL) / ADV) + oy, x = x0 + ox;
               const bool ok = (!guard || y < Hout) &&

@@ -73,17 +73,29 @@ def test_single_split_non_finite(K):
     assert (np.abs(O[ok] - O64[ok]) <= 1e-6 * A64[ok]).all()
 
 
-@pytest.mark.parametrize("scale", [1e-37, 1e-30, 1e30])
-@pytest.mark.parametrize("K", [7, 11])
+# Factors of the input and of the filters: normal values whose low bits lie
+# below the smallest bf16, denormal ones, large ones (single products above
+# 2^96), each against the other operand's, and sums that are denormal.
+SCALES = [(1e-30, 1), (1e-37, 1), (1, 1e-37), (1e-38, 1e20), (1e20, 1e-38), (1e-42, 1e30),
+          (1e30, 1e-42), (1e-20, 1e-20), (1e30, 1), (1, 1e36)]
+
+
+def scaled(x, scale):
+    return (x.astype(np.float64) * scale).astype(np.float32)
+
+
+@pytest.mark.parametrize("scale", SCALES, ids=str)
+@pytest.mark.parametrize("K", [6, 7, 11])
 def test_single_split_scales(K, scale):
-    """Values near the ends of the fp32 range: the low parts of 1e-37 are
-    denormal bf16 values (an absolute step of 2^-133, half of it per part)."""
+    """The bar of ordinary values at both ends of the fp32 range; a denormal
+    sum rounds once to a multiple of 2^-149."""
     Wx, Wy, M = 203, 50, 1
     I, F = random_arrays(1, M, Wx, Wy, K, seed=K + 7)
-    I, F = (I[0] * np.float32(scale)).astype(np.float32), F[:, 0]
+    I, F = scaled(I[0], scale[0]), scaled(F[:, 0], scale[1])
     O64, A64 = oracle_single(I, F)
     err = np.abs(gpu_single(I, F).astype(np.float64) - O64)
-    assert (err <= 1e-6 * A64 + K * K * 2.0 ** -133).all()
+    ok = A64 < 3e38
+    assert ok.any() and (err <= 1e-6 * A64 + 2.0 ** -149)[ok].all()
 
 
 # (C, M, Wx, Wy, K): channel counts around the stages of 8 to 128, filters
@@ -153,3 +165,18 @@ def test_multi_split_non_finite():
             assert np.array_equal(kind(O), kind(V)), (p, kind)
         ok = np.isfinite(V)
         assert np.allclose(O[ok], V[ok], rtol=1e-4, atol=1e-3)
+
+
+@pytest.mark.parametrize("scale", SCALES, ids=str)
+@pytest.mark.parametrize("layer", [(20, 40, 37, 21, 3), (9, 33, 23, 20, 5), (70, 5, 33, 9, 1)])
+def test_multi_split_scales(layer, scale):
+    """As test_single_split_scales, in every shape."""
+    I, F = random_arrays(*layer, seed=sum(layer) + 5)
+    I, F = scaled(I, scale[0]), scaled(F, scale[1])
+    O64, A64 = oracle_multi(I, F)
+    ok = A64 < 3e38
+    assert ok.any()
+    It, Ft = torch.from_numpy(I).cuda(), torch.from_numpy(F).cuda()
+    for p in split_plans(*layer):
+        err = np.abs(dc.multi(It, Ft, plan=p).cpu().numpy().astype(np.float64) - O64)
+        assert (err <= 3e-6 * A64 + 2.0 ** -149)[ok].all(), p
