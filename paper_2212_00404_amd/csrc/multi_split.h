@@ -74,6 +74,52 @@ struct SplitCfg {
   static constexpr int RED = RED_IN ? 4 * BV : AF;
 };
 
+typedef float floatx16s __attribute__((ext_vector_type(16)));
+
+// A wave group's part (one of WK) of the sums of a 32 x 32 tile, straight from
+// memory with fp32 matrix instructions: taken where the sum of the triples is
+// not finite, it gives what the fp32 kernels give.  Every lane of the wave
+// takes part: its filter m + lane % 32, its pixel (y, x), inside the map, and
+// every second channel.  Bound by the loads of the filters (64 lines each): one
+// infinity in 512 -> 512 channels, 40 x 40, K = 3: 205 us (545 where one wave
+// group sums alone, 2898 with a sum per lane and filter in turn; a finite
+// input 67), 64 -> 64 channels of 512 x 512 NaN 344 us (2442; finite 119).
+template <int K, int WK>
+__device__ __forceinline__ floatx16s sum_again(const float *__restrict__ I,
+                                               const float *__restrict__ F, const TileArgs &a,
+                                               int m, int y, int x, int wk) {
+  constexpr int KK = K * K, CB = K >= 8 ? 1 : 8 / K;  // channel pairs loaded at once
+  const int lane = threadIdx.x & 63, g = lane >> 5;
+  const size_t plane = (size_t)a.Wy * a.Wx;
+  const float *Fm = F + (size_t)min(m + (lane & 31), a.M - 1) * a.C * KK;
+  const float *Ip = I + (size_t)y * a.Wx + x;
+  floatx16s f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) f[v] = 0.f;
+#pragma unroll 1
+  for (int c0 = 2 * CB * wk; c0 < a.C; c0 += 2 * CB * WK)
+#pragma unroll 1
+    for (int r = 0; r < K; ++r) {
+      float iv[CB][K], fv[CB][K];
+#pragma unroll
+      for (int q = 0; q < CB; ++q) {
+        const int c = c0 + 2 * q + g, cl = min(c, a.C - 1);
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+          iv[q][s] = Ip[cl * plane + (size_t)r * a.Wx + s];
+          fv[q][s] = Fm[cl * KK + r * K + s];
+          if (c >= a.C) iv[q][s] = fv[q][s] = 0.f;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < CB; ++q)
+#pragma unroll
+        for (int s = 0; s < K; ++s)
+          f = __builtin_amdgcn_mfma_f32_32x32x2f32(fv[q][s], iv[q][s], f, 0, 0, 0);
+    }
+  return f;
+}
+
 template <int K, int NB, int WM, int WN, int WK, int KB>
 __global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void multi_split(
     const float *__restrict__ I, const float *__restrict__ F, float *__restrict__ O, TileArgs a) {
@@ -167,7 +213,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void m
     b_base[nb] = p < npix ? mul24(ty, a.IW) + p - mul24(ty, a.tpx) : 0;
   }
 
-  typedef float acc_t __attribute__((ext_vector_type(16)));
+  typedef floatx16s acc_t;
   acc_t acc[NB], cor[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
@@ -375,6 +421,29 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void m
   mark(4);
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) acc[nb] += cor[nb];
+  struct Pixel { int y, x; bool ok; };
+  auto pixel = [&](int nb) __attribute__((always_inline)) {
+    const int p = (wn * NB + nb) * 32 + col;
+    const int ty = fdiv(p, a.tpx, inv_tpx);
+    const int gy = py0 + ty, gx = px0 + p - mul24(ty, a.tpx);
+    return Pixel{gy, gx, p < npix && gy < Hout && gx < Wout};
+  };
+  // whether a sum that is stored is not finite
+  auto any_bad = [&](int nb) __attribute__((always_inline)) {
+    float z = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) z = fmaf(0.f, acc[nb][v], z);
+    return __any(pixel(nb).ok && !(z == 0.f));
+  };
+  // this wave group's part of the sums again
+  auto again = [&](int nb) __attribute__((always_inline)) {
+    const Pixel p = pixel(nb);
+    return sum_again<K, WK>(I, F, a, m0 + wm * 32, min(p.y, Hout - 1), min(p.x, Wout - 1), wk);
+  };
+  auto replace = [&](int nb, const acc_t &f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f * acc[nb][v] == 0.f ? acc[nb][v] : f[v];
+  };
   // Fixed-order sum of the WK wave groups, in as many passes as one buffer
   // takes.
   if constexpr (WK > 1) {
@@ -383,53 +452,65 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void m
     static_assert(PER >= 1, "a wave group's sums fit a buffer");
     float *red = Cfg::RED_IN ? reinterpret_cast<float *>(in0) : fa0;
     const int wmn = wm + WM * wn;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    auto add_groups = [&](acc_t &sum, auto &&added) __attribute__((always_inline)) {
       for (int g0 = 1; g0 < WK; g0 += PER) {
         if (wk >= g0 && wk < g0 + PER) {
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            red[(wk - g0) * TILE + (wmn * 16 + v) * 64 + lane] = acc[nb][v];
+            red[(wk - g0) * TILE + (wmn * 16 + v) * 64 + lane] = sum[v];
         }
         lds_barrier();
         if (wk == 0) {
           for (int q = g0; q < min(g0 + PER, WK); ++q)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-              acc[nb][v] += red[(q - g0) * TILE + (wmn * 16 + v) * 64 + lane];
+              sum[v] += red[(q - g0) * TILE + (wmn * 16 + v) * 64 + lane];
+          if (g0 + PER >= WK) added();
         }
         lds_barrier();
       }
+    };
+    // Group 0 tells the others, which otherwise are done here, of sums that are
+    // not finite: all groups sum those again.
+    int *flags = reinterpret_cast<int *>(in1);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      add_groups(acc[nb], [&]() __attribute__((always_inline)) {
+        acc[nb] *= kSplitUnscale;
+        const int bad = any_bad(nb);
+        if (lane == 0) flags[nb * WM * WN + wmn] = bad;
+      });
+    int bad = 0;
+#pragma unroll
+    for (int i = 0; i < NB * WM * WN; ++i) bad |= flags[i];
+    if (__builtin_amdgcn_readfirstlane(bad)) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        acc_t f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) f[v] = 0.f;
+        const int mine = __builtin_amdgcn_readfirstlane(flags[nb * WM * WN + wmn]);
+        if (mine) f = again(nb);
+        add_groups(f, [&]() __attribute__((always_inline)) { if (mine) replace(nb, f); });
+      }
+    }
     if (wk != 0) return;
+  } else {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      acc[nb] *= kSplitUnscale;
+      if (any_bad(nb)) replace(nb, again(nb));
+    }
   }
 
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const int p = (wn * NB + nb) * 32 + col;
-    const int ty = fdiv(p, a.tpx, inv_tpx);
-    const int gy = py0 + ty, gx = px0 + p - mul24(ty, a.tpx);
-    const bool ok = p < npix && gy < Hout && gx < Wout;
-    acc[nb] *= kSplitUnscale;
-    float z = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) z = fmaf(0.f, acc[nb][v], z);
-    if (ok && !(z == 0.f)) {
-      // a non-finite sum: again from memory, one fp32 FMA per term
-      for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm * 32 + Mfma<32>::row(lane, v);
-        if (m >= a.M) continue;
-        float f = 0.f;
-        const float *Fm = F + (size_t)m * ckk;
-        for (int c = 0; c < a.C; ++c)
-          for (int t = 0; t < KK; ++t)
-            f = fmaf(I[c * plane + (size_t)(gy + t / K) * a.Wx + gx + t % K], Fm[c * KK + t], f);
-        O[((size_t)m * Hout + gy) * Wout + gx] = f;
-      }
-    } else if (ok) {
+    const Pixel p = pixel(nb);
+    if (p.ok) {
       // one offset per lane, the filters' planes in scalar registers
       const size_t map = (size_t)Hout * Wout;
       const int mw = m0 + wm * 32;
-      float *Ol = O + ((size_t)gy * Wout + gx) + 4 * g * map;
+      float *Ol = O + ((size_t)p.y * Wout + p.x) + 4 * g * map;
       if (mw + 32 <= a.M) {
 #pragma unroll
         for (int v = 0; v < 16; ++v)

@@ -68,14 +68,71 @@ template <int K> struct Patch {
   static_assert(2 * NQ >= PH + K - 1, "the steps cover the window");
 };
 
+// The sums of a strip (its patches from column x0 and row y0 of map O, the columns
+// from x_own stored) that came out non-finite, again from memory, one fp32 FMA
+// per tap.  It runs once the strip is stored and reads the stored values back,
+// so that the strip's own code only gathers a flag.  A window's row is loaded
+// at once, 16 bytes at a time (bound by the vector L1): a 4096 x 4096 map of
+// NaN 164 us at K = 7 and 205 at K = 11 (543 and 592 with 4-byte loads; 1374 and
+// 1815 with a load and an FMA after the other at each patch row).
+template <int K>
+__device__ __forceinline__ void sum_again(const float *I, const float *F, float *O, int Wx, int Wy,
+                                          int x0, int x_own, int y0, int nv) {
+  constexpr int PW = Patch<K>::PW, PH = Patch<K>::PH;
+  const int Hout = Wy - K + 1, Wout = Wx - K + 1;
+  // the lane's outputs of a patch row, as in the strip's stores; the lane number
+  // read anew, so that nothing per lane stays in registers through the strip
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int j = tid & 15, g = (tid & 63) >> 4;
+  const int oy = PW == 8 ? g >> 1 : g, x = x0 + PW * j + (PW == 8 ? 4 * (g & 1) : 0);
+  __threadfence_block();
+#pragma unroll 1
+  for (int y = y0 + oy; y < min(y0 + nv * PH, Hout); y += PH) {
+    float *Or = O + (size_t)y * Wout + x;
+    bool bad[4], any = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      bad[e] = x + e >= x_own && x + e < Wout && !(0.f * Or[e] == 0.f);
+      any = any || bad[e];
+    }
+    if (!any) continue;
+    const float *Ir = I + (size_t)y * Wx;
+    float f[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int r = 0; r < K; ++r, Ir += Wx) {
+      float w[K + 3];
+      if (x + 4 <= Wout) {
+        constexpr int V = (K + 3) / 4;
+#pragma unroll
+        for (int q = 0; q < V; ++q) {
+          const floatx4u p = *reinterpret_cast<const floatx4u *>(Ir + x + 4 * q);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) w[4 * q + i] = p[i];
+        }
+#pragma unroll
+        for (int i = 4 * V; i < K + 3; ++i) w[i] = Ir[x + i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < K + 3; ++i) w[i] = Ir[min(x + i, Wx - 1)];
+      }
+#pragma unroll
+      for (int s = 0; s < K; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = fmaf(w[s + e], F[r * K + s], f[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (bad[e]) Or[e] = f[e];
+  }
+}
+
 // Strips of `nv` patch rows, numbered along x, then y; a workgroup's waves take
 // four in turn.  nstrips: all of them.
 template <int K>
-__global__ __launch_bounds__(kBlock, 2) void single_split(const float *__restrict__ I,
-                                                          const float *__restrict__ F,
-                                                          float *__restrict__ O, int Wx, int Wy,
-                                                          int M, int strips_x, int nstrips,
-                                                          int m_per_block, int nv) {
+__global__ __launch_bounds__(kBlock, 2) void single_split(
+    const float *__restrict__ I, const float *__restrict__ F, float *__restrict__ O, int Wx,
+    int Wy, int M, int strips_x, int nstrips, int m_per_block, int nv) {
   using S = Patch<K>;
   constexpr int PW = S::PW, PH = S::PH, NQ = S::NQ, ADV = S::ADV, NS = S::NS, P = S::P, NF = S::NF;
   const int Hout = Wy - K + 1, Wout = Wx - K + 1;
@@ -158,6 +215,7 @@ __global__ __launch_bounds__(kBlock, 2) void single_split(const float *__restric
       const uint32_t off_out = 4u * (uint32_t)(oy * Wout + ox);
 
       const bool whole = x0 + ox >= x_own, part = !whole && x0 + ox + 4 > x_own;
+      int bad = 0;  // 1: a sum was not finite
 
       // FULL: every column of the strip is stored; EDGE: those from x_own;
       // NARROW: the map is narrower than a strip (NARROW_END: loads clamped).
@@ -286,19 +344,11 @@ __global__ __launch_bounds__(kBlock, 2) void single_split(const float *__restric
                               (kind == FULL || (kind == EDGE ? whole || part : x < Wout));
               // zero times a finite value is zero, anything else NaN
               const float z = fmaf(0.f, r[0], fmaf(0.f, r[1], fmaf(0.f, r[2], 0.f * r[3])));
-              if (ok && !(z == 0.f)) {
-#pragma unroll 1
-                for (int e = 0; e < 4; ++e) {
-                  // from memory, one fp32 FMA per tap
-                  const float *Iw = I + (size_t)y * Wx + min(x + e, Wout - 1);
-                  float f = 0.f;
-#pragma unroll 1
-                  for (int k = 0; k < K * K; ++k) f = fmaf(Iw[(k / K) * Wx + k % K], Fm[k], f);
-                  r[0] = e == 0 ? f : r[0];
-                  r[1] = e == 1 ? f : r[1];
-                  r[2] = e == 2 ? f : r[2];
-                  r[3] = e == 3 ? f : r[3];
-                }
+              // (a branch, which the compiler keeps for the statement in it: without
+              // one it takes 6 more registers at K = 7, and so a third less waves)
+              if (__ballot(!(z == 0.f)) != 0) {
+                asm volatile("" : "+s"(bad));
+                bad = 1;
               }
               if constexpr (kind == FULL) {
                 if (ok)
@@ -344,6 +394,7 @@ __global__ __launch_bounds__(kBlock, 2) void single_split(const float *__restric
         strip(std::integral_constant<int, NARROW>{});
       else
         strip(std::integral_constant<int, NARROW_END>{});
+      if (bad != 0) sum_again<K>(I, Fm, O + (size_t)m * Hout * Wout, Wx, Wy, x0, x_own, y0, nv);
     }
   }
 }
