@@ -12,15 +12,19 @@
 namespace dconv {
 
 // Debug builds (-DDCONV_POISON_LDS, libdconv_poison.so): every LDS buffer of
-// a kernel starts filled with NaN, so an output computed from LDS that the
-// kernel did not write first (a missing copy, wait or barrier before the
-// first use of a buffer) comes out non-finite.  Ordinary builds: nothing.
+// a kernel starts filled with ones in every bit, NaN as fp32 and as bf16, so an
+// output computed from LDS that the kernel did not write first (a missing
+// copy, wait or barrier before the first use of a buffer) comes out non-finite;
+// and the kernels on bf16 triples leave non-finite sums as they are
+// (kSumAgain), which they otherwise take again from memory.  Ordinary builds:
+// nothing.
 #ifdef DCONV_POISON_LDS
+constexpr bool kSumAgain = false;
 template <class T>
 __device__ __forceinline__ void poison_lds(T *p, int n) {
-  float *f = reinterpret_cast<float *>(p);
-  const int nf = n * (int)(sizeof(T) / sizeof(float));
-  for (int i = threadIdx.x; i < nf; i += blockDim.x) f[i] = __builtin_nanf("");
+  uint32_t *w = reinterpret_cast<uint32_t *>(p);
+  const int nw = n * (int)(sizeof(T) / sizeof(uint32_t));
+  for (int i = threadIdx.x; i < nw; i += blockDim.x) w[i] = 0xffffffffu;
 }
 #define DCONV_POISON(...) \
   do {                    \
@@ -28,6 +32,7 @@ __device__ __forceinline__ void poison_lds(T *p, int n) {
     __syncthreads();      \
   } while (0)
 #else
+constexpr bool kSumAgain = true;
 #define DCONV_POISON(...) \
   do {                    \
   } while (0)

@@ -433,7 +433,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void m
     float z = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) z = fmaf(0.f, acc[nb][v], z);
-    return __any(pixel(nb).ok && !(z == 0.f));
+    return kSumAgain && __any(pixel(nb).ok && !(z == 0.f));
   };
   // this wave group's part of the sums again
   auto again = [&](int nb) __attribute__((always_inline)) {

@@ -394,7 +394,8 @@ __global__ __launch_bounds__(kBlock, 2) void single_split(
         strip(std::integral_constant<int, NARROW>{});
       else
         strip(std::integral_constant<int, NARROW_END>{});
-      if (bad != 0) sum_again<K>(I, Fm, O + (size_t)m * Hout * Wout, Wx, Wy, x0, x_own, y0, nv);
+      if (kSumAgain && bad != 0)
+        sum_again<K>(I, Fm, O + (size_t)m * Hout * Wout, Wx, Wy, x0, x_own, y0, nv);
     }
   }
 }

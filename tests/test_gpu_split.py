@@ -43,15 +43,27 @@ def test_single_split_edges(shape):
         assert rms[0] <= 1.1 * rms[1], rms
 
 
+# What surrounds the tensors in the tests of reads outside them: large, and
+# finite, because a non-finite sum would be taken again from the right places
+# (NaN around the tensors: test_gpu_poison.py, in a build that does not).
+OUTSIDE = 1e20
+
+
+def framed(x, offset=0):
+    """x on the GPU, `offset` floats off a 16-byte boundary, OUTSIDE before and after it."""
+    buf = torch.full((x.size + 2048,), OUTSIDE, device="cuda")
+    lo = 1024 + offset
+    buf[lo:lo + x.size] = torch.from_numpy(x).cuda().reshape(-1)
+    return buf[lo:lo + x.size].view(x.shape)
+
+
+@pytest.mark.parametrize("offset", [0, 1])
 @pytest.mark.parametrize("K", [5, 7, 9, 10, 13])
-def test_single_split_reads_stay_in_the_map(K):
-    """The map is the end of its allocation's rows: what lies past it is NaN
-    and must not reach any output."""
+def test_single_split_reads_stay_in_the_tensors(K, offset):
+    """What lies before and after both tensors reaches no output."""
     Wx, Wy, M = 150 - K, 37 + K, 2
     I, F = random_arrays(1, M, Wx, Wy, K, seed=K)
-    buf = torch.full((Wx * Wy + 4096,), float("nan"), device="cuda")
-    buf[:Wx * Wy] = torch.from_numpy(I[0]).cuda().reshape(-1)
-    O = dc.single(buf[:Wx * Wy].view(Wy, Wx), torch.from_numpy(F[:, 0]).cuda())
+    O = dc.single(framed(I[0], offset), framed(F[:, 0], offset))
     O64, A64 = oracle_single(I[0], F[:, 0])
     assert_within(O.cpu().numpy(), O64, A64, "K=%d" % K, rel=1e-6)
 
@@ -137,16 +149,16 @@ def test_multi_split_every_plan(layer):
             assert rms(O) <= 1.1 * base, (p, rms(O), base)
 
 
-@pytest.mark.parametrize("layer", [(17, 33, 21, 19, 3), (9, 34, 23, 20, 5), (70, 5, 33, 9, 1)])
-def test_multi_split_reads_stay_in_the_tensors(layer):
-    """What lies before and after both tensors is NaN and reaches no output."""
+# filters that start 4, 8 and 12 bytes off a 16-byte boundary, where the copies
+# of 16 bytes start anywhere too
+@pytest.mark.parametrize("offset", range(4))
+@pytest.mark.parametrize("layer", [(17, 33, 21, 19, 3), (9, 34, 23, 20, 5), (70, 5, 33, 9, 1),
+                                   (32, 70, 20, 13, 2), (16, 65, 19, 16, 7)])
+def test_multi_split_reads_stay_in_the_tensors(layer, offset):
+    """What lies before and after both tensors reaches no output."""
     C, M, Wx, Wy, K = layer
     I, F = random_arrays(C, M, Wx, Wy, K, seed=sum(layer))
-    def framed(x):
-        buf = torch.full((x.size + 2048,), float("nan"), device="cuda")
-        buf[1024:1024 + x.size] = torch.from_numpy(x).cuda().reshape(-1)
-        return buf[1024:1024 + x.size].view(x.shape)
-    It, Ft = framed(I), framed(F)
+    It, Ft = framed(I, (offset + 1) % 4), framed(F, offset)
     O64, A64 = oracle_multi(I, F)
     for p in split_plans(*layer):
         assert_within(dc.multi(It, Ft, plan=p).cpu().numpy(), O64, A64, str(p), rel=3e-6)
