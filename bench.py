@@ -561,10 +561,6 @@ def launch_plan(dc, w, variant, single_variant):
     """The plan the library uses for workload w (host logic)."""
     if w.kind == "multi":
         return dc.plan_multi(w.C, w.M, w.Wx, w.Wy, w.K, variant)
-    # An automatic call takes the matrix-core kernel from K = 9 on, with the plan
-    # that forcing it gives; the planner's automatic plan names the vector one.
-    if single_variant == "auto" and 9 <= w.K <= 11 and w.Wx % 4 == 0:
-        single_variant = "mfma"
     return dc.plan_single(w.Wx, w.Wy, w.K, w.M, variant=single_variant)
 
 

@@ -81,9 +81,9 @@ int dconv_single(const float *I, const float *F, float *O, int Wx, int Wy, int K
  * 16-byte aligned or Wx not a multiple of 4).  Other returns as for
  * dconv_single.
  *   DCONV_VARIANT_AUTO takes the matrix-core kernel wherever it is faster, at
- * K = 5 .. 13 and any alignment; the plans below describe the division of the
- * work for the families as they can be forced, so for K other than 7 the
- * automatic plan is the vector kernel's.
+ * K = 5 .. 13 and any alignment.  Values of 2^112 and above, infinities and NaN
+ * are handled as the vector family handles them, but slower (up to six times
+ * the time of finite values for a whole map of them).
  */
 int dconv_single_variant(const float *I, const float *F, float *O, int Wx, int Wy, int K,
                          int M, int variant, void *stream);
@@ -104,7 +104,10 @@ int dconv_multi(const float *I, const float *F, float *O, int C, int M, int Wx,
 /*
  * dconv_multi_variant -- dconv_multi with the kernel family forced
  * (DCONV_VARIANT_AUTO, _VALU or _MFMA), for A/B measurement of the vector
- * and matrix-core paths.  DCONV_EUNSUPPORTED if the forced family has no
+ * and matrix-core paths.  DCONV_VARIANT_MFMA forces the kernels on the fp32
+ * matrix instructions; those on three bf16 parts of each value (as accurate;
+ * K <= 7, plans of DCONV_VARIANT_MFMA with kernel ids from 16) belong to
+ * DCONV_VARIANT_AUTO.  DCONV_EUNSUPPORTED if the forced family has no
  * kernel for this K (the matrix-core family covers K <= 11).
  */
 int dconv_multi_variant(const float *I, const float *F, float *O, int C, int M,
@@ -133,14 +136,12 @@ typedef struct dconv_plan {
 } dconv_plan;
 
 /*
- * dconv_plan_single / dconv_plan_multi -- report the planner's plan for these
- * sizes on a device with `num_cu` compute units (<= 0: 256): what a call with
- * that plan runs, and what a call without one runs except where dconv_single
- * takes the matrix-core kernel instead (see dconv_single_variant).
+ * dconv_plan_single / dconv_plan_multi -- report the plan a call with these
+ * sizes would use on a device with `num_cu` compute units (<= 0: 256).
  * Validation is the same as for the compute calls.  `out` must not be NULL.
  */
 int dconv_plan_single(int Wx, int Wy, int K, int M, int num_cu, dconv_plan *out);
-/* The plan dconv_single_variant would use (the input assumed 16-byte aligned). */
+/* The plan dconv_single_variant would use (both: the input assumed 16-byte aligned). */
 int dconv_plan_single_variant(int Wx, int Wy, int K, int M, int variant, int num_cu,
                               dconv_plan *out);
 int dconv_plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_cu,
@@ -148,7 +149,7 @@ int dconv_plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_c
 
 /*
  * dconv_plan_multi_candidates -- every plan of a kernel family (both
- * families for DCONV_VARIANT_AUTO) that fits a device with `num_cu` compute
+ * families and the kernels on bf16 parts for DCONV_VARIANT_AUTO) that fits a device with `num_cu` compute
  * units: each workgroup shape, in a fixed order.  dconv_plan_multi returns
  * one of them (the planner's estimate is the smallest).  Writes min(count, capacity) plans to `out` (may be NULL when
  * capacity is 0) and the total to *count.  For autotuning (Section 3 divides
@@ -169,10 +170,10 @@ int dconv_multi_with_plan(const float *I, const float *F, float *O, int C, int M
 /*
  * dconv_plan_single_candidates -- every single-map plan for these sizes on a
  * device with `num_cu` compute units (<= 0: 256), the input assumed 16-byte
- * aligned with Wx a multiple of 4 (as dconv_plan_single_variant): each tile
- * shape of the vector kernel (tall or short tiles, 64 or 16 lanes across a
- * row) and, for DCONV_VARIANT_AUTO / _MFMA with K in 5..11, the matrix-core
- * kernel, crossed with the division of the M filters into groups of
+ * aligned (as dconv_plan_single_variant): each tile shape of the vector kernel
+ * (tall or short tiles, 64 or 16 lanes across a row) and the matrix-core
+ * kernel (for DCONV_VARIANT_AUTO with K in 5..13, for DCONV_VARIANT_MFMA where
+ * it can be forced), crossed with the division of the M filters into groups of
  * workgroups (Section 3.1 divides the filters over processors, or the map).
  * Fixed order; dconv_plan_single returns one of them.  Writes
  * min(count, capacity) plans to `out` (may be NULL when capacity is 0) and
@@ -184,10 +185,9 @@ int dconv_plan_single_candidates(int Wx, int Wy, int K, int M, int variant, int 
 /*
  * dconv_single_with_plan -- dconv_single with a plan chosen by the caller,
  * which must equal (field by field) one of the candidates for these sizes on
- * the current device and for the alignment of I (a 16-byte-aligned input
- * with Wx a multiple of 4 has the candidates of
- * dconv_plan_single_candidates; other inputs have the single-float staging
- * kernel's); DCONV_EINVAL otherwise.  Semantics and returns as for
+ * the current device and for the alignment of I (a 16-byte-aligned input has
+ * the candidates of dconv_plan_single_candidates; for others the vector
+ * kernel's are the single-float staging kernel's); DCONV_EINVAL otherwise.  Semantics and returns as for
  * dconv_single.
  */
 int dconv_single_with_plan(const float *I, const float *F, float *O, int Wx, int Wy, int K,

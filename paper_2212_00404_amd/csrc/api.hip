@@ -78,12 +78,8 @@ DCONV_EXPORT int dconv_single_variant(const float *I, const float *F, float *O, 
   if ((rc = current_num_cu(&num_cu)) != DCONV_OK) return rc;
   dconv::SinglePlan p;
   const bool aligned = (reinterpret_cast<uintptr_t>(I) & 15) == 0;
-  if (variant == DCONV_VARIANT_AUTO && dconv::single_takes_split(Wx, Wy, K, M, aligned)) {
-    dconv::plan_single_split(Wx, Wy, K, M, num_cu, 0, &p);
-  } else {
-    rc = dconv::plan_single(Wx, Wy, K, M, num_cu, aligned, variant, &p);
-    if (rc != DCONV_OK) return rc;
-  }
+  rc = dconv::plan_single(Wx, Wy, K, M, num_cu, aligned, variant, &p);
+  if (rc != DCONV_OK) return rc;
   // A launch error still pending from earlier work in this thread is
   // cleared first, so DCONV_EHIP reports this call's launch only.
   (void)hipGetLastError();

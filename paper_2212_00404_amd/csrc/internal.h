@@ -84,19 +84,17 @@ constexpr int kMaxTiledK = 11;
 int plan_single(int Wx, int Wy, int K, int M, int num_cu, bool aligned, int variant,
                 SinglePlan *p);
 // Every single-map plan for these sizes (each tile shape of the family the
-// input's alignment allows, and the matrix-core kernel where it exists,
-// crossed with the division of the filters over workgroups), in a fixed
-// order; plan_single picks one of them.
+// input's alignment allows, and the matrix-core kernel where it exists, with
+// DCONV_VARIANT_MFMA where it can be forced, crossed with the division of the
+// filters over workgroups), in a fixed order; plan_single picks one of them.
 int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, int variant,
                       std::vector<SinglePlan> &out);
 hipError_t launch_single(const SinglePlan &p, const float *I, const float *F, float *O,
                          int Wx, int Wy, int M, hipStream_t s);
 // The matrix-core kernel (single_split.hip, K = kSplitMinK .. kSplitMaxK, any
 // alignment): its plan (the filters in `force_splits` groups, 0: the number
-// the time model prefers), launch, and whether a call that forces neither a
-// family nor a plan takes it.
+// the time model prefers), launch, and whether the automatic plan takes it.
 constexpr int kSplitMinK = 5, kSplitMaxK = 13;
-constexpr int kSplitPlanMinK = 5;  // smallest K of the plans offered for it
 void plan_single_split(int Wx, int Wy, int K, int M, int num_cu, int force_splits, SinglePlan *p);
 bool single_takes_split(int Wx, int Wy, int K, int M, bool aligned);
 hipError_t launch_single_split(const SinglePlan &p, const float *I, const float *F, float *O,

@@ -463,19 +463,21 @@ hipError_t launch_tiled(const SinglePlan &p, const float *I, const float *F, flo
 
 }  // namespace
 
+// Where the matrix-core kernel can be forced (the automatic choice and its plans
+// reach it at K = kSplitMinK .. kSplitMaxK and any alignment).
+static bool can_force_split(int K, bool vec4) {
+  return vec4 && K >= kSplitMinK && K <= kMaxTiledK;
+}
+
 int plan_single(int Wx, int Wy, int K, int M, int num_cu, bool aligned, int variant,
                 SinglePlan *p) {
   *p = SinglePlan{};
   p->K = K;
   // 16-byte aligned rows: whole float4 staging loads.
   const bool vec4 = aligned && (Wx % 4 == 0);
-  // The plans of the matrix-core kernel keep to K = 5 .. 11 and rows of whole
-  // float4; a call that forces neither family nor plan takes that kernel
-  // wherever it is faster (single_takes_split).
-  const bool can_mfma = vec4 && K >= kSplitPlanMinK && K <= kMaxTiledK;
-  if (variant == DCONV_VARIANT_MFMA && !can_mfma) return DCONV_EUNSUPPORTED;
-  if (variant == DCONV_VARIANT_MFMA || (variant == DCONV_VARIANT_AUTO && can_mfma && K == 7 &&
-                                        single_takes_split(Wx, Wy, K, M, aligned))) {
+  if (variant == DCONV_VARIANT_MFMA && !can_force_split(K, vec4)) return DCONV_EUNSUPPORTED;
+  if (variant == DCONV_VARIANT_MFMA ||
+      (variant == DCONV_VARIANT_AUTO && single_takes_split(Wx, Wy, K, M, aligned))) {
     plan_single_split(Wx, Wy, K, M, num_cu, 0, p);
     return DCONV_OK;
   }
@@ -590,13 +592,13 @@ int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, in
   if (num_cu <= 0) num_cu = 256;
   const bool vec4 = aligned && (Wx % 4 == 0);
   const bool valu = variant != DCONV_VARIANT_MFMA;
-  const bool mfma = variant != DCONV_VARIANT_VALU && vec4 && K >= kSplitPlanMinK && K <= kMaxTiledK;
-  if (K > kMaxTiledK) {
-    if (!valu) return DCONV_EUNSUPPORTED;
+  const bool split = variant == DCONV_VARIANT_MFMA
+                         ? can_force_split(K, vec4)
+                         : variant == DCONV_VARIANT_AUTO && K >= kSplitMinK && K <= kSplitMaxK;
+  if (valu && K > kMaxTiledK) {
     SinglePlan p;
     plan_single(Wx, Wy, K, M, num_cu, aligned, DCONV_VARIANT_VALU, &p);
     out.push_back(p);
-    return DCONV_OK;
   }
   switch (K) {
 #define DCONV_CANDIDATES_K(k)                                                    \
@@ -613,7 +615,7 @@ int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, in
     default:
       break;
   }
-  if (mfma) split_candidates(Wx, Wy, K, M, num_cu, out);
+  if (split) split_candidates(Wx, Wy, K, M, num_cu, out);
   return out.empty() ? DCONV_EUNSUPPORTED : DCONV_OK;
 }
 

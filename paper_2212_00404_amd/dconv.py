@@ -311,7 +311,7 @@ def plan_single(Wx: int, Wy: int, K: int, M: int, num_cu: int = 256,
 def plan_single_candidates(Wx: int, Wy: int, K: int, M: int, variant: str = "auto",
                            num_cu: int = 256) -> list:
     """Every plan ``dconv_single_with_plan`` accepts for these sizes (a
-    16-byte-aligned input with Wx % 4 == 0; host logic)."""
+    16-byte-aligned input; host logic)."""
     n = ctypes.c_int(0)
     lib = load()
     _check(lib.dconv_plan_single_candidates(Wx, Wy, K, M, _VARIANTS[variant], num_cu, None, 0,

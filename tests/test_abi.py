@@ -178,17 +178,30 @@ def test_single_plan_shapes(shape):
             dc.plan_single(*shape, variant="mfma")
 
 
-def test_single_auto_takes_the_matrix_cores_at_k7_only():
-    """The automatic single-map plan runs the matrix-core kernel at K = 7,
-    where it measured faster than the vector kernel on a 4096 x 4096 map, and
-    the vector kernel for every other K (and for rows that are not whole
-    float4, which the matrix-core kernel cannot stage)."""
-    for K in range(1, 12):
-        assert dc.plan_single(4096, 4096, K, 1)["kernel"] == (3 if K == 7 else 0), K
-        if K >= 5:
+def test_single_automatic_plan_names_the_matrix_cores_where_a_call_takes_them():
+    """The automatic single-map plan is what a call runs: the matrix-core kernel
+    (3) from K = 6 on a 4096 x 4096 map, at K = 8 on tall maps, at K = 7 and 9 on
+    all but small ones, at K = 5, 6 where rows are not whole float4, up to
+    K = 13; the vector kernel's two forms (0, 2) and the generic one (1)
+    elsewhere."""
+    for K in range(1, 16):
+        assert dc.plan_single(4096, 4096, K, 1)["kernel"] == (0 if K < 6 else 3 if K < 14 else 1), K
+        assert dc.plan_single(4097, 4096, K, 1)["kernel"] == (2 if K < 5 else 3 if K < 14 else 1), K
+        if 5 <= K <= 11:
             assert dc.plan_single(4096, 4096, K, 1, variant="mfma")["kernel"] == 3
-    # rows of 4097 floats: the vector kernel's unaligned-row form
-    assert dc.plan_single(4097, 4096, 7, 1)["kernel"] == 2
+    for (Wx, Wy, K, M), kernel in [((256, 256, 6, 4), 0), ((1024, 400, 8, 9), 0), ((135, 60, 8, 5), 2),
+                                   ((135, 70, 8, 5), 3), ((32, 55, 7, 16), 0), ((32, 55, 9, 16), 0),
+                                   ((33, 55, 9, 16), 3), ((13, 13, 13, 1), 3)]:
+        assert dc.plan_single(Wx, Wy, K, M)["kernel"] == kernel, (Wx, Wy, K, M)
+
+
+@pytest.mark.parametrize("shape", [(4096, 4096, 9, 1), (1021, 1003, 5, 8), (77, 51, 13, 4), (40, 40, 12, 3),
+                                   (135, 70, 8, 5), (28, 28, 6, 512), (300, 200, 11, 70), (64, 64, 14, 2)])
+def test_automatic_single_plan_is_a_listed_one(shape):
+    for num_cu in (32, 256):
+        cands = dc.plan_single_candidates(*shape, num_cu=num_cu)
+        assert dc.plan_single(*shape, num_cu=num_cu) in cands
+        assert len(cands) == len({tuple(sorted(p.items())) for p in cands})
 
 
 @pytest.mark.parametrize("shape", [

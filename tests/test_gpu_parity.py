@@ -23,8 +23,8 @@ MULTI = sorted(n for n, w in WORKLOADS.items() if w.kind == "multi")
 
 
 def single_families(Wx, K):
-    """Kernel families dconv_single can run for this shape (the matrix-core
-    family needs K in 5..11 and rows of a multiple of 4 floats)."""
+    """Kernel families that can be forced for this shape (the matrix-core one for
+    K in 5..11 and rows of a multiple of 4 floats), and the automatic choice."""
     return ["auto", "valu"] + (["mfma"] if 5 <= K <= 11 and Wx % 4 == 0 else [])
 
 
@@ -326,7 +326,7 @@ def test_misaligned_base_pointers(offsets):
         for fam in single_families(Wx, K):
             flat, Ot = _offset_view(np.zeros(O64.shape, np.float32), oo, dev)
             if fam == "mfma" and oi % 4:
-                # the matrix-core kernel stages whole 16-byte rows
+                # the matrix-core kernel can be forced on rows of whole 16 bytes only
                 with pytest.raises(RuntimeError, match="cannot run"):
                     dc.single(It, Ft, out=Ot, variant=fam)
                 continue

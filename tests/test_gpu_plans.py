@@ -9,7 +9,7 @@ import torch
 
 import paper_2212_00404_amd as dc
 from dconv_workloads import random_arrays
-from gpu_util import assert_exact, oracle_multi, oracle_single
+from gpu_util import assert_exact, assert_within, oracle_multi, oracle_single
 from private_layers import PRIVATE_LAYERS
 
 pytestmark = pytest.mark.gpu
@@ -111,6 +111,22 @@ def test_every_single_candidate_plan_is_exact(layer):
     torch.cuda.synchronize()
     for p, o in zip(cands, outs):
         assert_exact(o.cpu().numpy(), O64, "%r plan %r" % (layer, p))
+
+
+@pytest.mark.parametrize("layer", [(1021, 203, 5, 3), (260, 100, 6, 2), (135, 70, 8, 5), (300, 90, 9, 3),
+                                   (301, 90, 11, 2), (76, 50, 12, 2), (77, 51, 13, 4), (40, 36, 14, 2)],
+                         ids=str)
+def test_automatic_single_plan_is_what_a_call_runs(layer):
+    """A call without a plan and one with the plan that the planner names give
+    the same bits, and every other candidate the same sums."""
+    Wx, Wy, K, M = layer
+    I, F = random_arrays(1, M, Wx, Wy, K, seed=sum(layer) * 19)
+    It, Ft = torch.from_numpy(I[0]).cuda(), torch.from_numpy(F[:, 0]).cuda()
+    O64, A64 = oracle_single(I[0], F[:, 0])
+    auto = dc.single(It, Ft)
+    assert torch.equal(auto, dc.single(It, Ft, plan=dc.plan_single(Wx, Wy, K, M)))
+    for p in dc.plan_single_candidates(Wx, Wy, K, M):
+        assert_within(dc.single(It, Ft, plan=p).cpu().numpy(), O64, A64, "%r %r" % (layer, p))
 
 
 def test_foreign_single_plan_is_rejected():

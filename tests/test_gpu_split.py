@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 
 # (Wx, Wy, K, M); rows of 4n + 1 .. 3 floats take the kernel at K = 5 and 6 too
 SINGLE = [(k, k, k, 1) for k in range(10, 14)] + [
-    (131, 9, 5, 1), (133, 40, 5, 7), (129, 30, 6, 3), (134, 134, 7, 2), (135, 21, 8, 5),
+    (131, 9, 5, 1), (133, 40, 5, 7), (129, 30, 6, 3), (134, 134, 7, 2), (135, 70, 8, 5), (1024, 600, 8, 6),
     (137, 22, 9, 1), (136, 70, 9, 2), (73, 13, 10, 1), (74, 77, 11, 3), (75, 50, 12, 2),
     (77, 51, 13, 4), (301, 211, 11, 1), (1025, 33, 7, 9), (515, 600, 9, 40), (64, 1000, 10, 3),
     (41, 39, 9, 600), (2050, 67, 13, 1)]
@@ -30,6 +30,7 @@ SINGLE = [(k, k, k, 1) for k in range(10, 14)] + [
 @pytest.mark.parametrize("shape", SINGLE, ids=[str(s) for s in SINGLE])
 def test_single_split_edges(shape):
     Wx, Wy, K, M = shape
+    assert dc.plan_single(Wx, Wy, K, M)["kernel"] == 3
     I, F = random_arrays(1, M, Wx, Wy, K, seed=sum(shape) * 31, variant="int")
     assert_exact(gpu_single(I[0], F[:, 0]), oracle_single(I[0], F[:, 0])[0], str(shape))
     I, F = random_arrays(1, M, Wx, Wy, K, seed=sum(shape) * 37)
