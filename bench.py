@@ -195,6 +195,12 @@ def autotune(names, steps, warmup, report_out=None):
         write_autotune_report(results, report_out)
 
 
+def matrix_core_plans(dc, layer):
+    """Every plan of a multi-channel layer on the matrix cores: those on the fp32
+    instructions and those on bf16 triples."""
+    return [p for p in dc.plan_multi_candidates(*layer) if p["variant"] == 2]
+
+
 def heldout(n, steps, warmup, seed=7, report_out=None):
     """The planner on seeded random layer shapes (seed 7: shapes it was not
     fitted on): C, M in 32..512,
@@ -226,7 +232,7 @@ def heldout(n, steps, warmup, seed=7, report_out=None):
         F = torch.randn((M, C, K, K), device=dev, generator=g) * (2.0 / (C * K * K)) ** 0.5
         O = torch.empty((M, Wy - K + 1, Wx - K + 1), device=dev)
         times = {}
-        for p in dc.plan_multi_candidates(C, M, Wx, Wy, K, "mfma"):
+        for p in matrix_core_plans(dc, (C, M, Wx, Wy, K)):
             for _ in range(max(1, warmup)):
                 dc.multi(I, F, out=O, plan=p)
             torch.cuda.synchronize()
