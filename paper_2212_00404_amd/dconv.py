@@ -192,9 +192,11 @@ def _require(t: torch.Tensor, name: str, ndim: int):
 
 
 # What torch.cuda.current_stream(device).cuda_stream and torch.cuda.current_device()
-# give, without the objects they build: a small call is bound by the host.
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# give, without the objects they build: a small call is bound by the host.  (A
+# torch without a GPU build has neither, and no tensor that reaches them; the
+# planner and the model need none.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 class _OnDevice:

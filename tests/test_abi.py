@@ -4,6 +4,8 @@ grids cover every output and fit the gfx950 limits (host logic only)."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -327,3 +329,22 @@ def test_automatic_multi_plan_is_a_listed_one(layer, split):
         plan = dc.plan_multi(*layer, num_cu=num_cu)
         assert plan in dc.plan_multi_candidates(*layer, num_cu=num_cu)
     assert (plan["variant"] == 2 and plan["kernel"] >= 16) == split
+
+
+def test_host_logic_needs_no_gpu_build_of_torch():
+    """The planner is host arithmetic: it loads beside a torch without the GPU
+    entry points that the compute calls use."""
+    code = ("import torch\n"
+            "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    if hasattr(torch._C, n): delattr(torch._C, n)\n"
+            "import paper_2212_00404_amd as dc\n"
+            "assert dc.plan_multi(64, 64, 30, 30, 3)['grid_x'] > 0\n"
+            "try:\n"
+            "    dc.single(torch.zeros(4, 4), torch.zeros(1, 3, 3))\n"
+            "except ValueError as e:\n"
+            "    assert 'must be on a HIP device' in str(e)\n"
+            "else:\n"
+            "    raise AssertionError('a CPU tensor was accepted')\n")
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True,
+                         timeout=300)
+    assert res.returncode == 0, res.stderr
