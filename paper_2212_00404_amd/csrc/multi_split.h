@@ -45,21 +45,21 @@ constexpr int split_b_vec(int K, int PT, int CC) { return 3 * (CC / 8) * split_p
 constexpr int split_lds(int K, int MT, int PT, int CC) {
   return 2 * (4 * split_a_floats(K, MT, CC) + 16 * split_b_vec(K, PT, CC));
 }
-// Channels per stage: the most of 8, 16, 32, 64, 128 whose two buffers fit the LDS
-// (0: none).
-constexpr int split_cc(int K, int MT, int PT, int cap_kb) {
+// Channels per stage: the most of 8, 16, 32, 64, 128 whose two buffers fit the
+// 160 KB of LDS (0: none).
+constexpr int split_cc(int K, int MT, int PT) {
   int best = 0;
   for (int cc = 8; cc <= 128; cc *= 2)
-    if (split_lds(K, MT, PT, cc) <= cap_kb * 1024) best = cc;
+    if (split_lds(K, MT, PT, cc) <= 160 * 1024) best = cc;
   return best;
 }
 
-template <int K, int NB, int WM, int WN, int WK, int KB>
+template <int K, int NB, int WM, int WN, int WK>
 struct SplitCfg {
   static constexpr int KK = K * K;
   static constexpr int NW = WM * WN * WK, NTHR = 64 * NW;
   static constexpr int MT = 32 * WM, PT = 32 * NB * WN;
-  static constexpr int CC = split_cc(K, MT, PT, KB);
+  static constexpr int CC = split_cc(K, MT, PT);
   static constexpr int G = CC / 8;
   static constexpr int FROW = split_frow(K, CC), FP = split_pitch(K, CC);
   static constexpr int AF = split_a_floats(K, MT, CC);      // floats of a filter buffer
@@ -120,10 +120,10 @@ __device__ __forceinline__ floatx16s sum_again(const float *__restrict__ I,
   return f;
 }
 
-template <int K, int NB, int WM, int WN, int WK, int KB>
-__global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void multi_split(
+template <int K, int NB, int WM, int WN, int WK>
+__global__ __launch_bounds__(64 * WM * WN * WK, WM *WN *WK / 4) void multi_split(
     const float *__restrict__ I, const float *__restrict__ F, float *__restrict__ O, TileArgs a) {
-  using Cfg = SplitCfg<K, NB, WM, WN, WK, KB>;
+  using Cfg = SplitCfg<K, NB, WM, WN, WK>;
   constexpr int KK = Cfg::KK, NW = Cfg::NW, NTHR = Cfg::NTHR, MT = Cfg::MT, CC = Cfg::CC;
   constexpr int G = Cfg::G, FROW = Cfg::FROW, FP = Cfg::FP, AF = Cfg::AF, NA = Cfg::NA;
   constexpr int PIX = Cfg::PIX, NU = Cfg::NU, ITEMS = Cfg::ITEMS, KS = Cfg::KS;
@@ -528,20 +528,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 160 / KB *WM *WN *WK / 4) void m
 
 // Workgroup shapes: 32 WM filters x 32 NB WN pixels, WK wave groups sharing a
 // stage's items.
-struct SplitShape { int NB, WM, WN, WK, KB; };
+struct SplitShape { int NB, WM, WN, WK; };
 constexpr SplitShape kSplitShapes[] = {
-    {2, 2, 4, 1, 160},  // 64 x 256
-    {2, 2, 2, 2, 160},  // 64 x 128
-    {2, 1, 2, 4, 160},  // 32 x 128
-    {2, 2, 1, 4, 160},  // 64 x 64
-    {2, 1, 1, 8, 160},  // 32 x 64
-    {1, 1, 1, 8, 160},  // 32 x 32
+    {2, 2, 4, 1},  // 64 x 256
+    {2, 2, 2, 2},  // 64 x 128
+    {2, 1, 2, 4},  // 32 x 128
+    {2, 2, 1, 4},  // 64 x 64
+    {2, 1, 1, 8},  // 32 x 64
+    {1, 1, 1, 8},  // 32 x 32
 };
 constexpr int kNumSplit = sizeof(kSplitShapes) / sizeof(kSplitShapes[0]);
 
 template <int K, int S>
 using SplitShapeCfg = SplitCfg<K, kSplitShapes[S].NB, kSplitShapes[S].WM, kSplitShapes[S].WN,
-                               kSplitShapes[S].WK, kSplitShapes[S].KB>;
+                               kSplitShapes[S].WK>;
 
 template <int K, int S>
 hipError_t launch_split_shape(const MultiPlan &p, const float *I, const float *F, float *O,
@@ -550,7 +550,7 @@ hipError_t launch_split_shape(const MultiPlan &p, const float *I, const float *F
   if constexpr (SplitShapeCfg<K, S>::CC == 0) {
     return hipErrorInvalidValue;
   } else {
-    auto kern = multi_split<K, sh.NB, sh.WM, sh.WN, sh.WK, sh.KB>;
+    auto kern = multi_split<K, sh.NB, sh.WM, sh.WN, sh.WK>;
     hipLaunchKernelGGL(kern, dim3(p.grid_x), dim3(64 * sh.WM * sh.WN * sh.WK), 0, st, I, F, O, a);
     return hipGetLastError();
   }
