@@ -425,11 +425,15 @@ int plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_cu, Mul
     if (all[k].first < all[best].first) best = k;
   double bound = std::numeric_limits<double>::infinity();
   if (!all.empty()) {
-    // estimate() is too high for some private-stage plans.  Of 71 random layers
-    // the three over such a plan of eight or more waves had bf16 triples at 0.79
-    // to 0.89 of it and ran 1.2 to 1.5 times slower on them (45 x 80, C = 390,
-    // M = 40, K = 3: 21.9 against 26.3 us); of those with four waves one at 0.99
-    // ran 1.04 times slower.  All others ran 1.0 to 2.2 times faster.
+    // estimate() is too high for some private-stage plans, most with eight or more
+    // waves and K = 3.  Random layers, the triples' time over the fp32 plan's:
+    //   eight waves or more   estimates below 0.75: 0.65 to 1.14 (10 layers,
+    //       geometric mean 0.86), to 0.9: 0.47 (57 -> 98 channels, 91 x 99,
+    //       K = 5) to 1.41 (461 -> 72, 75 x 75, K = 3; 28, mean 1.03), above:
+    //       mean 1.17 (22)
+    //   four waves            below 0.97: 0.56 to 1.13 (57, mean 0.81), above:
+    //       0.83, 1.01, 1.03
+    //   shared stages         0.51 to 0.91 (30)
     const MultiPlan &q = all[best].second;
     const bool priv = q.block == 64 * q.waves_c;
     bound = all[best].first * (!priv ? 1.0 : q.waves_c >= 8 ? 0.75 : 0.97);
