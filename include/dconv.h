@@ -31,6 +31,10 @@
  *     pointers never touch the device.
  *   - Results are accumulated in fp32 in a fixed order for a given shape and
  *     device, so repeated calls give bitwise identical output.
+ *   - Infinities, NaN and values of any magnitude give what fp32 multiply-adds
+ *     give.  The kernels on bf16 parts take sums that reach infinities, NaN,
+ *     inputs of 2^112 and above or sums of 2^96 and above a second time, so
+ *     such calls are slower (up to seven times where all of a map's sums do).
  *   - The library allocates no device memory and needs no workspace: every
  *     call reads and writes the caller's three tensors only (and the latency
  *     probe its own two arguments).
@@ -81,9 +85,7 @@ int dconv_single(const float *I, const float *F, float *O, int Wx, int Wy, int K
  * 16-byte aligned or Wx not a multiple of 4).  Other returns as for
  * dconv_single.
  *   DCONV_VARIANT_AUTO takes the matrix-core kernel wherever it is faster, at
- * K = 5 .. 13 and any alignment.  Values of 2^112 and above, infinities and NaN
- * are handled as the vector family handles them, but slower (up to six times
- * the time of finite values for a whole map of them).
+ * K = 5 .. 13 and any alignment.
  */
 int dconv_single_variant(const float *I, const float *F, float *O, int Wx, int Wy, int K,
                          int M, int variant, void *stream);

@@ -49,7 +49,9 @@ constexpr bool kSumAgain = true;
 // clock at [6 + 5s + i]: i = 0 stage start, 1 after the copy wait, 2 after
 // the barrier, 3 after issuing the next stage's copies, 4 after the MFMAs
 // (shapes whose waves stage their own channels pass no barrier and issue
-// the next stage's copies halfway through the MFMAs, between marks 3 and 4).
+// the next stage's copies halfway through the MFMAs, between marks 3 and 4;
+// the kernels on bf16 triples, which fetch between their steps: i = 0 stage
+// start, 1 first step, 2 middle step, 3 last step, 4 its end).
 // Ordinary builds: none of this.
 constexpr int kStageTraceStages = 64;
 constexpr int kStageTraceWords = 6 + 5 * kStageTraceStages;
