@@ -282,8 +282,8 @@ def copy_probe(mib, steps):
 # TCC counters per run).
 COUNTER_PASSES = (
     ("trace", ["--kernel-trace", "--stats"]),
-    ("sq_mfma", ["--kernel-trace", "--pmc", "SQ_WAVES", "SQ_INSTS_VALU_MFMA_F32",
-                 "SQ_INSTS_VALU_MFMA_MOPS_F32", "SQ_VALU_MFMA_BUSY_CYCLES", "SQ_INSTS_LDS",
+    ("sq_mfma", ["--kernel-trace", "--pmc", "SQ_WAVES", "SQ_INSTS_VALU_MFMA_MOPS_F32",
+                 "SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_VALU_MFMA_BUSY_CYCLES", "SQ_INSTS_LDS",
                  "SQ_LDS_BANK_CONFLICT", "SQ_BUSY_CYCLES", "GRBM_GUI_ACTIVE"]),
     ("sq_valu", ["--kernel-trace", "--pmc", "SQ_WAVES", "SQ_INSTS_VALU", "SQ_INSTS_VALU_FMA_F32",
                  "SQ_INSTS_LDS", "SQ_LDS_BANK_CONFLICT", "SQ_BUSY_CYCLES", "GRBM_GUI_ACTIVE"]),
@@ -491,7 +491,8 @@ def counter_report(root, out_path=None):
         dur = r["avg_us"] * 1e-6
         busy = r.get("SQ_VALU_MFMA_BUSY_CYCLES")
         busy = busy / SIMDS / (dur * CLOCK_GHZ * 1e9) if busy else None
-        mops = r.get("SQ_INSTS_VALU_MFMA_MOPS_F32")
+        # kernels on bf16 triples: six products each
+        mops = r.get("SQ_INSTS_VALU_MFMA_MOPS_F32") or r.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0) / 6
         issued = mops * 512 / w.flops if mops else None
         fma = r.get("SQ_INSTS_VALU_FMA_F32")
         fma_tf = fma * 64 * 2 / dur / 1e12 if fma else None
@@ -521,7 +522,8 @@ def counter_report(root, out_path=None):
                   COPY_PROBE_MIB, COPY_PROBE_MIB, fmt(fscale, "%.4f"), fmt(wscale, "%.4f"),
                   cal.get("fetch", ("-",))[0][:60]),
               "MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / SIMDs / (duration x clock); issued / "
-              "algorithmic = SQ_INSTS_VALU_MFMA_MOPS_F32 x 512 / (2*C*M*K*K*outputs); FMA "
+              "algorithmic = SQ_INSTS_VALU_MFMA_MOPS_F32 x 512 / (2*C*M*K*K*outputs) (kernels on "
+              "bf16 triples: a sixth of SQ_INSTS_VALU_MFMA_MOPS_BF16); FMA "
               "TFLOP/s = SQ_INSTS_VALU_FMA_F32 x 64 lanes x 2 / duration; VALU busy = "
               "SQ_INSTS_VALU x 4 clocks / SIMDs / (duration x clock); conflict cycles per LDS "
               "instruction = SQ_LDS_BANK_CONFLICT / SQ_INSTS_LDS."]
@@ -1093,7 +1095,9 @@ def stage_trace(workload, warmup, report_out=None):
                  "the next stage's copies, MFMAs = the stage's matrix instructions (plans whose "
                  "waves stage their own channels, `w` equal to the wave count: no barrier, and "
                  "the copies are issued halfway through the MFMAs, so the MFMA phase holds "
-                 "them).  Setup = "
+                 "them; plans on bf16 triples, k16 on, fetch between their steps and pass the barrier "
+                 "after the last: the four columns are stage start to first step, the first half of "
+                 "the steps, the second up to the last, and the last step).  Setup = "
                  "kernel start to the first copies; first copies = issuing stage 0; span = "
                  "kernel start to end of wave 0 (wall clock).", "",
                  "| workload | plan | workgroups | stages | clock GHz | setup | first copies | "
