@@ -4,7 +4,7 @@
 //
 // What bounds the fp32 kernel (multi_kernels.h) on large layers is the fp32
 // matrix rate: six bf16 instructions do the work of eight fp32 ones in 192
-// clocks where those take 512.  The price is the split, 44 vector
+// clocks where those take 512.  The price is the split, 52 vector
 // instructions per eight values and lane, so each value is split as few
 // times as possible and its parts are reused:
 //   * Input: a workgroup's halo tile of CC channels is loaded into registers
@@ -15,7 +15,7 @@
 //   * Filters: F[m][c0 : c0 + CC] is copied to LDS as it is (direct 16-byte
 //     copies, rows at an odd float4 pitch); a wave reads the eight channels of a tap
 //     of its 32 filters, splits them and uses them for NB tiles of 32 pixels.
-//     With NB = 2 the split (44 instructions against 12 matrix instructions)
+//     With NB = 2 the split (52 instructions against 12 matrix instructions)
 //     hides behind the matrix pipe, which leaves about six issue slots per
 //     instruction.
 // The 16 values of k of an instruction are two items of eight channels: item

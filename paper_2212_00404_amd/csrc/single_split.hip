@@ -420,7 +420,7 @@ hipError_t launch_k(const SinglePlan &p, const float *I, const float *F, float *
 //             than half a strip wide, where a wave is mostly empty (32 x 55, 16
 //             filters: 4.9 against 6.0 us)
 //   K = 8     (the steps of K = 9 for fewer taps) faster on tall maps (35.2 ->
-//             27.9 us); short ones up to 1.25x slower (1755 x 39, 272 filters)
+//             27.9 us); short ones up to 1.35x slower (1755 x 39, 272 filters)
 //   K = 6     faster from about 1.5M outputs (4096 x 4096: 29.0 -> 25.3 us;
 //             below, up to 1.4x slower), and wherever rows are not whole float4
 //   K = 5     only where rows are not whole float4, which the vector kernel
