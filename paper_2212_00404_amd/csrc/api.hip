@@ -120,9 +120,7 @@ DCONV_EXPORT int dconv_single_with_plan(const float *I, const float *F, float *O
   if ((rc = current_num_cu(&num_cu)) != DCONV_OK) return rc;
   std::vector<dconv::SinglePlan> all;
   const bool aligned = (reinterpret_cast<uintptr_t>(I) & 15) == 0;
-  if (dconv::single_candidates(Wx, Wy, K, M, num_cu, aligned, DCONV_VARIANT_AUTO, all) !=
-      DCONV_OK)
-    return DCONV_EINVAL;
+  dconv::single_candidates_like(Wx, Wy, K, M, num_cu, aligned, *plan, all);
   for (const auto &p : all) {
     dconv_plan e;
     dconv::export_single_plan(p, &e);
@@ -181,8 +179,7 @@ DCONV_EXPORT int dconv_multi_with_plan(const float *I, const float *F, float *O,
   int num_cu = 0;
   if ((rc = current_num_cu(&num_cu)) != DCONV_OK) return rc;
   std::vector<dconv::MultiPlan> all;
-  if (dconv::multi_candidates(C, M, Wx, Wy, K, DCONV_VARIANT_AUTO, num_cu, all) != DCONV_OK)
-    return DCONV_EINVAL;
+  dconv::multi_candidates_like(C, M, Wx, Wy, K, *plan, num_cu, all);
   for (const auto &p : all) {
     dconv_plan e;
     dconv::export_multi_plan(p, &e);

@@ -91,6 +91,10 @@ int plan_single(int Wx, int Wy, int K, int M, int num_cu, bool aligned, int vari
 // filters over workgroups), in a fixed order; plan_single picks one of them.
 int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, int variant,
                       std::vector<SinglePlan> &out);
+// The candidates that a public plan can be equal to, those of its family and
+// division of the filters (running a plan searches them on every call).
+void single_candidates_like(int Wx, int Wy, int K, int M, int num_cu, bool aligned,
+                            const dconv_plan &like, std::vector<SinglePlan> &out);
 hipError_t launch_single(const SinglePlan &p, const float *I, const float *F, float *O,
                          int Wx, int Wy, int M, hipStream_t s);
 // The matrix-core kernel (single_split.hip, K = kSplitMinK .. kSplitMaxK, any
@@ -126,6 +130,11 @@ int plan_multi(int C, int M, int Wx, int Wy, int K, int variant, int num_cu, Mul
 // fits the device, in a fixed order; plan_multi picks one of them.
 int multi_candidates(int C, int M, int Wx, int Wy, int K, int variant, int num_cu,
                      std::vector<MultiPlan> &out);
+// The candidates that a public plan can be equal to: those of its family and of
+// its kind of kernel.  (Running a plan searches them on every call: 2 to 4 us
+// over all of them.)
+void multi_candidates_like(int C, int M, int Wx, int Wy, int K, const dconv_plan &like, int num_cu,
+                           std::vector<MultiPlan> &out);
 // The public description of a plan.
 void export_multi_plan(const MultiPlan &p, dconv_plan *out);
 hipError_t launch_multi(const MultiPlan &p, const float *I, const float *F, float *O, int C,

@@ -259,12 +259,14 @@ TileChoice choose_split_tile(int Hout, int Wout, int cap, int pix, int K) {
 // Shapes that cannot come out below `bound` whatever their tile are left out
 // (a planner's best so far; a list of every plan passes infinity).  Planning is
 // part of every call: without the bound it took 2.6 us on a 9 x 9 layer.
+// only: that shape alone (-1: all).
 void enumerate_split(int C, int M, int Wx, int Wy, int K, int num_cu, double bound,
-                     std::vector<std::pair<double, MultiPlan>> &out) {
+                     std::vector<std::pair<double, MultiPlan>> &out, int only = -1) {
   if (K > kSplitMaxFilter) return;
   if ((int64_t)Wx * Wy >= (int64_t(1) << 29)) return;  // 32-bit byte offsets
   const int Hout = Wy - K + 1, Wout = Wx - K + 1;
   for (int i = 0; i < kNumSplit; ++i) {
+    if (only >= 0 && i != only) continue;
     const SplitShape sh = kSplitShapes[i];
     const SplitConsts sc = split_consts(i, K);
     if (sc.cc == 0) continue;
@@ -481,6 +483,24 @@ int multi_candidates(int C, int M, int Wx, int Wy, int K, int variant, int num_c
   out.clear();
   for (const auto &e : all) out.push_back(e.second);
   return out.empty() ? DCONV_EUNSUPPORTED : DCONV_OK;
+}
+
+void multi_candidates_like(int C, int M, int Wx, int Wy, int K, const dconv_plan &like, int num_cu,
+                           std::vector<MultiPlan> &out) {
+  if (like.kernel == kGenericKernel) {  // a candidate only where there is no other
+    multi_candidates(C, M, Wx, Wy, K, DCONV_VARIANT_AUTO, num_cu, out);
+    return;
+  }
+  std::vector<std::pair<double, MultiPlan>> all;
+  if (like.variant == DCONV_VARIANT_VALU)
+    enumerate_family(C, M, Wx, Wy, K, false, num_cu, all);
+  else if (like.variant == DCONV_VARIANT_MFMA && like.kernel >= kSplitKernel)
+    enumerate_split(C, M, Wx, Wy, K, num_cu, std::numeric_limits<double>::infinity(), all,
+                    like.kernel - kSplitKernel);
+  else if (like.variant == DCONV_VARIANT_MFMA && K <= kMfmaMaxK)
+    enumerate_family(C, M, Wx, Wy, K, true, num_cu, all);
+  out.clear();
+  for (const auto &e : all) out.push_back(e.second);
 }
 
 hipError_t launch_multi(const MultiPlan &p, const float *I, const float *F, float *O, int C,

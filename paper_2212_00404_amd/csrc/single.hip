@@ -567,13 +567,16 @@ void tiled_candidates(int Wx, int Wy, int M, int num_cu, std::vector<SinglePlan>
   }
 }
 
-// The matrix-core kernel's plans for the same divisions of the filters.
-void split_candidates(int Wx, int Wy, int K, int M, int num_cu, std::vector<SinglePlan> &out) {
+// The matrix-core kernel's plans for the same divisions of the filters
+// (tile_m: those of that many filters per workgroup only, 0: all).
+void split_candidates(int Wx, int Wy, int K, int M, int num_cu, int tile_m,
+                      std::vector<SinglePlan> &out) {
   std::vector<int> splits{0};
   for (int s = 1; s < M; s *= 2) splits.push_back(s);
   splits.push_back(M);
   const size_t first = out.size();
   for (int s : splits) {
+    if (tile_m > 0 && s > 0 && (M + s - 1) / s != tile_m) continue;
     SinglePlan p{};
     plan_single_split(Wx, Wy, K, M, num_cu, s, &p);
     bool dup = false;
@@ -615,8 +618,18 @@ int single_candidates(int Wx, int Wy, int K, int M, int num_cu, bool aligned, in
     default:
       break;
   }
-  if (split) split_candidates(Wx, Wy, K, M, num_cu, out);
+  if (split) split_candidates(Wx, Wy, K, M, num_cu, 0, out);
   return out.empty() ? DCONV_EUNSUPPORTED : DCONV_OK;
+}
+
+void single_candidates_like(int Wx, int Wy, int K, int M, int num_cu, bool aligned,
+                            const dconv_plan &like, std::vector<SinglePlan> &out) {
+  out.clear();
+  if (like.variant == DCONV_VARIANT_VALU)
+    single_candidates(Wx, Wy, K, M, num_cu, aligned, DCONV_VARIANT_VALU, out);
+  else if (like.variant == DCONV_VARIANT_MFMA && like.tile_m > 0 && K >= kSplitMinK &&
+           K <= kSplitMaxK)
+    split_candidates(Wx, Wy, K, M, num_cu, like.tile_m, out);
 }
 
 void export_single_plan(const SinglePlan &p, dconv_plan *out) {
